@@ -7,10 +7,10 @@
 // chunk the lane reloads the segment's checkpoint, runs the forward step without
 // outputs up to the chunk, then over the chunk while recording a tape in
 // registers -- per frame the blend's d = m' - x and a 16-bit word holding the
-// table slot, hitA and swap -- and finally sweeps the chunk backwards, reading
+// table offset, hitA and swap -- and finally sweeps the chunk backwards, reading
 // the upstream gradient of bg and writing the gradient of the frame.  All of a
 // chunk's frame loads are issued before its replay and its gradient loads
-// before its sweep (with FP64 state during the replay, last frame first, the
+// before its sweep or in two halves before and within it (last frame first, the
 // order the sweep reads them), so their HBM latency overlaps.  With K <= KC
 // each frame is replayed once; longer segments replay a prefix per chunk.
 //
@@ -20,20 +20,27 @@
 // reproducible run to run and independent of the backward's launch shape.
 #include <type_traits>
 
-#include "dsgm_internal.h"
+#include "dsgm_fwd_impl.h"
 
 namespace dsgm {
 
 namespace {
 
-// With FP32 state the kernel is compiled for at least 4 waves per SIMD (at most
-// 128 VGPRs), which fits without spills once the upstream gradients are loaded
-// in two halves (below): BF16 frames ran 4 % faster than at 3 waves, FP32
-// frames the same.  FP64 state keeps the compiler's choice: its tape alone
-// takes 64 VGPRs, and neither the split loads nor 3 waves per SIMD (which
-// spill) were faster.
+// Waves per SIMD the kernel is compiled for.  FP32 state: 4 (at most 128
+// VGPRs), which fits with the upstream gradients loaded in two halves (below).
+// FP64 state: 3 (167 VGPRs with a 32-frame tape); the chain of a replayed frame
+// leaves a SIMD idle at 2: on 96 frames of 1080 x 1920, FP32 arrays, 650 us
+// against 700.  F32X2 keeps the compiler's choice (2).
+template <typename Acc>
+constexpr int bwd_waves() {
+  return is_f32x2<Acc>::value ? 1 : sizeof(Acc) == 4 ? 4 : 3;
+}
+
+// The frames, the upstream gradients and the gradients of the frames pass
+// through once: nontemporal (FP32 state 112 against 119 us on 128 frames of
+// 480 x 640, FP64 state 632 against 650 us on the frames above).
 template <typename In, typename Acc, typename Io, int KC, bool HAS_GBG, bool HAS_GST>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(Acc) == 4 ? 4 : 1)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bwd_waves<Acc>())))
 bwd_kernel(const BwdArgs a) {
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
   for (int i = threadIdx.x; i < TABLE_SIZE; i += blockDim.x)
@@ -76,63 +83,66 @@ bwd_kernel(const BwdArgs a) {
   const int64_t T = a.T, K = a.ckpt_every;
   const int64_t nseg = geom::n_segments(T, K);
 
-  // One chunk of `len` <= KC frames starting at c0, from state s: all of its
-  // frame loads are issued before the taped replay, all of its upstream bg
-  // gradient loads before the reverse sweep (FULL chunks need no per-frame
-  // guard).
-  auto chunk = [&](Model<Acc> s, const int64_t c0, const int len, auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
+  // A piece of N frames starting at c0, from state s: all of its frame loads
+  // are issued before the taped replay, all of its upstream bg gradient loads
+  // before the reverse sweep.  With the guard only the first `len` frames.
+  auto piece = [&](Model<Acc> s, const int64_t c0, const int len, auto n_tag, auto guard_tag) {
+    constexpr int N = decltype(n_tag)::value;
+    constexpr bool ALL = !decltype(guard_tag)::value;
     // frames and upstream gradients are held in their storage types (half the
     // registers of FP64 when the arrays are FP32) and widened at use
-    In xs[KC];
-    Io gb[KC];
+    In xs[N];
+    Io gb[N];
 #pragma unroll
-    for (int i = 0; i < KC; ++i)
-      if (FULL || i < len) xs[i] = *reinterpret_cast<const In*>(frames + (c0 + i) * fs_in + off_in);
+    for (int i = 0; i < N; ++i)
+      if (ALL || i < len)
+        xs[i] = fwd::ld_stream<In, 1>(
+            reinterpret_cast<const In*>(frames + (c0 + i) * fs_in + off_in)).v[0];
     // the upstream gradients are requested in the order the sweep uses them,
-    // last frame first; with FP32 state those of frames [LATE, KC) after the
-    // replay and [0, LATE) once the sweep reaches frame LATE - 1 (fewer
-    // registers live)
-    constexpr int LATE = sizeof(Acc) == 4 ? KC / 2 : 0;
+    // last frame first: one after each replayed frame (EARLY: FP64 arrays and
+    // F32X2 state), or those of frames [LATE, N) after the replay and [0, LATE)
+    // once the sweep reaches frame LATE - 1 (fewer registers live)
+    constexpr bool EARLY = sizeof(Io) == 8 || is_f32x2<Acc>::value;
+    constexpr int LATE = EARLY ? 0 : N / 2;
     auto load_gb = [&](const int j) {
       gb[j] = Io(0);
-      if (HAS_GBG && (FULL || j < len))
-        gb[j] = *reinterpret_cast<const Io*>(gbg + (c0 + j) * fs_io + off_io);
+      if (HAS_GBG && (ALL || j < len))
+        gb[j] = fwd::ld_stream<Io, 1>(
+            reinterpret_cast<const Io*>(gbg + (c0 + j) * fs_io + off_io)).v[0];
     };
-    Acc tape_d[KC];
-    uint32_t tape_m[(KC + 1) / 2];
+    Acc tape_d[N];
+    uint32_t tape_m[(N + 1) / 2];
 #pragma unroll
-    for (int i = 0; i < KC; ++i) {
-      if (FULL || i < len) {
-        const StepRecord<Acc> r = step_rec<Acc, false>(s, to_acc<In, Acc>(xs[i]), k, tbl);
+    for (int i = 0; i < N; ++i) {
+      if (ALL || i < len) {
+        const StepRecord<Acc> r = step_rec<Acc>(s, to_acc<In, Acc>(xs[i]), k, tbl);
         tape_d[i] = r.d;
-        const uint32_t m = uint32_t(r.idx) | (r.hitA ? 0x200u : 0u) | (r.swap ? 0x400u : 0u);
+        // the table offset is a multiple of 16: its low bits hold the flags
+        const uint32_t m = uint32_t(r.idx) | (r.hitA ? 1u : 0u) | (r.swap ? 2u : 0u);
         if (i % 2 == 0)
           tape_m[i / 2] = m;
         else
           tape_m[i / 2] |= m << 16;
       }
-      // FP64 state: frame i's value is dead now and the gradient the sweep
-      // needs i-th goes out, so the loads overlap the rest of the replay
-      if constexpr (LATE == 0) load_gb(KC - 1 - i);
+      if constexpr (EARLY) load_gb(N - 1 - i);
     }
-    if constexpr (LATE > 0) {
+    if constexpr (!EARLY) {
 #pragma unroll
-      for (int j = KC - 1; j >= LATE; --j) load_gb(j);
+      for (int j = N - 1; j >= LATE; --j) load_gb(j);
     }
 #pragma unroll
-    for (int i = KC - 1; i >= 0; --i) {
-      if constexpr (LATE > 0) {
-        if (i == LATE - 1) {
+    for (int i = N - 1; i >= 0; --i) {
+      if (LATE > 0 && i == LATE - 1) {
 #pragma unroll
-          for (int j = LATE - 1; j >= 0; --j) load_gb(j);
-        }
+        for (int j = LATE - 1; j >= 0; --j) load_gb(j);
       }
-      if (FULL || i < len) {
+      if (ALL || i < len) {
         const uint32_t m = (tape_m[i / 2] >> (16 * (i % 2))) & 0xFFFFu;
-        const Acc gx = reverse_step<Acc, HAS_GBG>(adj, Acc(gb[i]), tape_d[i], int(m & 0x1FFu),
-                                                  (m & 0x200u) != 0, (m & 0x400u) != 0, tbl);
-        *reinterpret_cast<Io*>(gfr + (c0 + i) * fs_io + off_io) = Io(gx);  // rounded once
+        const int idx = int(m & 0xFFF0u);
+        const Acc gx = reverse_step<Acc, HAS_GBG>(adj, Acc(gb[i]), tape_d[i], idx, (m & 1u) != 0,
+                                                  (m & 2u) != 0, entry_at(tbl, idx));
+        fwd::st_stream<Io, 1>(reinterpret_cast<Io*>(gfr + (c0 + i) * fs_io + off_io),
+                              Vec<Io, 1>{{Io(gx)}});  // rounded once
       }
     }
   };
@@ -141,33 +151,57 @@ bwd_kernel(const BwdArgs a) {
     const geom::Range sg = geom::segment(seg, T, K);
     const int64_t s0 = sg.lo;
     const char* base = ck + seg * a.ckpt_slot_bytes;
-    const int64_t nchunk = geom::n_chunks(sg, KC);
-    for (int64_t c = nchunk - 1; c >= 0; --c) {
-      const geom::Range ch = geom::chunk(sg, c, KC);
-      const int64_t c0 = ch.lo, c1 = ch.hi;
+    // the segment's state before frame c0: its checkpoint, replayed (only when
+    // the segment is longer than the tape, or in a short last piece) eight
+    // frames of loads at a time
+    auto state_at = [&](const int64_t c0) {
       Model<Acc> s;
       s.mA = reinterpret_cast<const Acc*>(base + 0 * a.ckpt_fplane)[g];
       s.vA = reinterpret_cast<const Acc*>(base + 1 * a.ckpt_fplane)[g];
       s.mC = reinterpret_cast<const Acc*>(base + 2 * a.ckpt_fplane)[g];
       s.vC = reinterpret_cast<const Acc*>(base + 3 * a.ckpt_fplane)[g];
-      s.aA = reinterpret_cast<const uint8_t*>(base + 4 * a.ckpt_fplane)[g];
-      s.aC = reinterpret_cast<const uint8_t*>(base + 4 * a.ckpt_fplane + a.ckpt_aplane)[g];
-      // replay up to the chunk (only when segments are longer than the tape),
-      // eight frames of loads at a time
+      s.aA = age_in<Acc>(reinterpret_cast<const uint8_t*>(base + 4 * a.ckpt_fplane)[g]);
+      s.aC = age_in<Acc>(
+          reinterpret_cast<const uint8_t*>(base + 4 * a.ckpt_fplane + a.ckpt_aplane)[g]);
       int64_t t = s0;
       for (; t + 8 <= c0; t += 8) {
         Acc xr[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) xr[i] = x_at(t + i);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) (void)step_rec<Acc, false>(s, xr[i], k, tbl);
+        for (int i = 0; i < 8; ++i) (void)step_rec<Acc>(s, xr[i], k, tbl);
       }
-      for (; t < c0; ++t) (void)step_rec<Acc, false>(s, x_at(t), k, tbl);
-      const int len = int(c1 - c0);
-      if (len == KC)
-        chunk(s, c0, len, std::true_type{});
-      else
-        chunk(s, c0, len, std::false_type{});
+      for (; t < c0; ++t) (void)step_rec<Acc>(s, x_at(t), k, tbl);
+      return s;
+    };
+    const int64_t nchunk = geom::n_chunks(sg, KC);
+    for (int64_t c = nchunk - 1; c >= 0; --c) {
+      const geom::Range ch = geom::chunk(sg, c, KC);
+      const int len = int(ch.hi - ch.lo);
+      using Whole = std::integral_constant<int, KC>;
+      if (len == KC) {
+        piece(state_at(ch.lo), ch.lo, len, Whole{}, std::false_type{});
+      } else if constexpr (is_f32x2<Acc>::value) {
+        // guarded frames: the pieces below made this form 15-20 % slower, its
+        // code being too large for the instruction cache as it is
+        piece(state_at(ch.lo), ch.lo, len, Whole{}, std::true_type{});
+      } else {
+        // a shorter chunk is cut into pieces whose lengths are the powers of
+        // two of its length, the longest first in time: a compile-time length
+        // needs no guard (FP32 state spilled 80 registers with guards)
+        int64_t c0 = ch.hi;
+        auto part = [&](auto n_tag) {
+          constexpr int N = decltype(n_tag)::value;
+          if ((len & N) == 0) return;
+          c0 -= N;
+          piece(state_at(c0), c0, N, n_tag, std::false_type{});
+        };
+        part(std::integral_constant<int, 1>{});
+        part(std::integral_constant<int, 2>{});
+        part(std::integral_constant<int, 4>{});
+        part(std::integral_constant<int, 8>{});
+        if constexpr (KC > 16) part(std::integral_constant<int, 16>{});
+      }
     }
   }
   static_cast<Io*>(a.gs0_mean_a)[g] = Io(adj.gmA);

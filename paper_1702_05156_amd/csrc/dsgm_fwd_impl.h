@@ -118,8 +118,8 @@ __device__ __forceinline__ void store_state(char* const planes[6], int64_t soff,
     vA.v[j] = s[j].vA;
     mC.v[j] = s[j].mC;
     vC.v[j] = s[j].vC;
-    aA.v[j] = uint8_t(s[j].aA);
-    aC.v[j] = uint8_t(s[j].aC);
+    aA.v[j] = age_out<Acc>(s[j].aA);
+    aC.v[j] = age_out<Acc>(s[j].aC);
   }
   *reinterpret_cast<Vec<Acc, P>*>(planes[0] + soff * int64_t(sizeof(Acc))) = mA;
   *reinterpret_cast<Vec<Acc, P>*>(planes[1] + soff * int64_t(sizeof(Acc))) = vA;
@@ -145,8 +145,8 @@ __device__ __forceinline__ void load_state(const GroupJob& j, Model<Acc>* s) {
     s[q].vA = vA.v[q];
     s[q].mC = mC.v[q];
     s[q].vC = vC.v[q];
-    s[q].aA = aA.v[q];
-    s[q].aC = aC.v[q];
+    s[q].aA = age_in<Acc>(aA.v[q]);
+    s[q].aC = age_in<Acc>(aC.v[q]);
   }
 }
 
@@ -182,8 +182,8 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
       s[q].vA = vA.v[q];
       s[q].mC = mC.v[q];
       s[q].vC = vC.v[q];
-      s[q].aA = aA.v[q];
-      s[q].aC = aC.v[q];
+      s[q].aA = age_in<Acc>(aA.v[q]);
+      s[q].aC = age_in<Acc>(aC.v[q]);
     }
   }
 
@@ -208,31 +208,28 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
       }
       --ck_left;
     }
-    Vec<uint8_t, P> mk;
     Vec<Io, P> bgv;
     Vec<uint8_t, P> cd;
     // the P pixels' exchanges share one wavefront-uniform branch
-    Acc xs[P], qd[P];
+    Acc xs[P];
     StepRecord<Acc> r[P];
-    bool any = false;
+    uint64_t any = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       xs[q] = to_acc<In, Acc>(xin.v[q]);
       r[q] = step_core<Acc>(s[q], xs[q], k, tbl);
-      qd[q] = mask_dist<Acc>(r[q]);
-      any |= r[q].swap;
+      any |= r[q].swap_lanes;
     }
-    if (any_lane(any)) {
+    if (any != 0) {
 #pragma unroll
-      for (int q = 0; q < P; ++q) {
-        apply_swap<Acc>(s[q], xs[q], k, r[q].swap);
-        qd[q] = mask_dist_swapped<Acc>(r[q], s[q], xs[q], qd[q]);
-      }
+      for (int q = 0; q < P; ++q) exchange<Acc>(s[q], xs[q], k, r[q]);
     }
+    uint64_t back[P];  // lanes whose pixel q is background
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      r[q].fg = fg_from<Acc, PRINTED>(qd[q], s[q], xs[q], k);
-      mk.v[q] = r[q].fg ? uint8_t(255) : uint8_t(0);
+      const bool b = bg_from<Acc, PRINTED>(r[q].qd, s[q], xs[q], k);
+      back[q] = __builtin_amdgcn_ballot_w64(b);
+      r[q].fg = !b;
       if (BG) bgv.v[q] = Io(s[q].mA);  // rounded once when Io is narrower
       if (CODES) cd.v[q] = uint8_t(code_of<Acc>(r[q]));
     }
@@ -242,11 +239,13 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
       // (exact, order-free) from the first lane; every caller has lane 0 active
       uint32_t n = 0;
 #pragma unroll
-      for (int q = 0; q < P; ++q) n += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(r[q].fg)));
+      for (int q = 0; q < P; ++q) n += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(true) & ~back[q]));
       if ((threadIdx.x & 63) == 0 && n != 0) atomicAdd(j.counts + t, n);
     }
     const int64_t o = t * fs;
-    st_stream<uint8_t, P>(reinterpret_cast<uint8_t*>(j.masks + o + j.foff), mk);
+    const auto mk = typename Raw<P>::type(mask_bytes<P>(back));
+    st_stream<uint8_t, P>(reinterpret_cast<uint8_t*>(j.masks + o + j.foff),
+                          __builtin_bit_cast(Vec<uint8_t, P>, mk));
     if (BG) st_stream<Io, P>(reinterpret_cast<Io*>(j.bg + o * int64_t(sizeof(Io)) + off_io), bgv);
     if (CODES) *reinterpret_cast<Vec<uint8_t, P>*>(j.codes + o + j.foff) = cd;
   };

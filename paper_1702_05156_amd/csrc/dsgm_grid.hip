@@ -48,8 +48,8 @@ __global__ void __launch_bounds__(256) grid_kernel(const GridArgs a) {
   s.vA = static_cast<const Acc*>(a.var_a)[blk];
   s.mC = static_cast<const Acc*>(a.mean_c)[blk];
   s.vC = static_cast<const Acc*>(a.var_c)[blk];
-  s.aA = a.age_a[blk];
-  s.aC = a.age_c[blk];
+  s.aA = age_in<Acc>(a.age_a[blk]);
+  s.aC = age_in<Acc>(a.age_c[blk]);
 
   const In* frames = static_cast<const In*>(a.frames);
   const int64_t base = y0 * a.row_stride + x0;
@@ -86,12 +86,12 @@ __global__ void __launch_bounds__(256) grid_kernel(const GridArgs a) {
     // Sec. 2.3 decisions on M, the Sec. 2.2 blend of the matched model with M
     const Acc dA = M - s.mA;
     const Acc dC = M - s.mC;
-    const bool hitA = (dA * dA < k.theta_s * s.vA) | (dA * dA < k.ts_vf);
-    const bool hitC = (dC * dC < k.theta_s * s.vC) | (dC * dC < k.ts_vf);
-    const int idx = hitA ? s.aA : (hitC ? s.aC : RESET_SLOT);
+    const bool hitA = lane_mask((dA * dA < k.theta_s * s.vA) | (dA * dA < k.ts_vf));
+    const bool hitC = lane_mask((dC * dC < k.theta_s * s.vC) | (dC * dC < k.ts_vf));
+    const int idx = hitA ? s.aA : (hitC ? s.aC : reset_age<Acc>());
     const Acc m = hitA ? s.mA : s.mC;
     const Acc v = hitA ? s.vA : s.vC;
-    const TableEntry<Acc> e = tbl[idx];
+    const TableEntry<Acc> e = entry_at(tbl, idx);
     const Acc mn = blend(e.u, m, e.w, M);
     // V: the block's largest squared distance from the updated mean; a reset
     // candidate has no V (its variance is var_init)
@@ -103,9 +103,9 @@ __global__ void __launch_bounds__(256) grid_kernel(const GridArgs a) {
         if (whole || (r < rows && c < cols)) {
           const Acc d = mn - I[r][c];
           const Acc q = d * d;
-          V = V < q ? q : V;
+          V = larger(V, q);
         }
-    V = idx == RESET_SLOT ? Acc(0) : V;
+    V = idx == reset_age<Acc>() ? Acc(0) : V;
     const Acc vn = blend(e.u, v, e.w, V) + e.r;
     const int an = e.next;
     s.mA = hitA ? mn : s.mA;
@@ -114,8 +114,12 @@ __global__ void __launch_bounds__(256) grid_kernel(const GridArgs a) {
     s.mC = hitA ? s.mC : mn;
     s.vC = hitA ? s.vC : vn;
     s.aC = hitA ? s.aC : an;
-    const bool swap = s.aC > s.aA;
-    if (any_lane(swap)) apply_swap<Acc>(s, M, k, swap);
+    const uint64_t swap_lanes = __builtin_amdgcn_ballot_w64(s.aC > s.aA);
+    const bool swap = __builtin_amdgcn_inverse_ballot_w64(swap_lanes);
+    if (swap_lanes != 0) {
+      Acc none = Acc(0);
+      swap_in_place<false>(s, M, k, swap_lanes, none);
+    }
 
     // per-pixel mask against the block's apparent model
 #pragma unroll
@@ -173,8 +177,8 @@ __global__ void __launch_bounds__(256) grid_kernel(const GridArgs a) {
   static_cast<Acc*>(a.var_a)[blk] = s.vA;
   static_cast<Acc*>(a.mean_c)[blk] = s.mC;
   static_cast<Acc*>(a.var_c)[blk] = s.vC;
-  a.age_a[blk] = uint8_t(s.aA);
-  a.age_c[blk] = uint8_t(s.aC);
+  a.age_a[blk] = age_out<Acc>(s.aA);
+  a.age_c[blk] = age_out<Acc>(s.aC);
 }
 
 template <typename In, typename Acc, typename Io>

@@ -128,11 +128,11 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
       s[q].vA = static_cast<const Acc*>(a.var_a)[pix + q];
       s[q].mC = static_cast<const Acc*>(a.mean_c)[pix + q];
       s[q].vC = static_cast<const Acc*>(a.var_c)[pix + q];
-      s[q].aA = a.age_a[pix + q];
-      s[q].aC = a.age_c[pix + q];
+      s[q].aA = age_in<Acc>(a.age_a[pix + q]);
+      s[q].aC = age_in<Acc>(a.age_c[pix + q]);
     } else {
       s[q].mA = s[q].vA = s[q].mC = s[q].vC = Acc(0);
-      s[q].aA = s[q].aC = 1;
+      s[q].aA = s[q].aC = age_in<Acc>(1);
     }
   }
 
@@ -239,22 +239,22 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
     }
 
     StepRecord<Acc> rec[PX];
-    bool any = false;
+    uint64_t any = 0;
 #pragma unroll
     for (int q = 0; q < PX; ++q) {
       rec[q] = step_core<Acc>(s[q], xs[q], k, tbl);
-      any |= rec[q].swap;
+      any |= rec[q].swap_lanes;
     }
-    if (any_lane(any)) {
+    if (any != 0) {
 #pragma unroll
-      for (int q = 0; q < PX; ++q) apply_swap<Acc>(s[q], xs[q], k, rec[q].swap);
+      for (int q = 0; q < PX; ++q) exchange<Acc>(s[q], xs[q], k, rec[q]);
     }
     Vec<uint8_t, PX> mk, cd;
     Vec<Io, PX> bgv;
     Vec<Io, PX> fv;  // the filtered frame in the array type
 #pragma unroll
     for (int q = 0; q < PX; ++q) {
-      rec[q].fg = fg_of<Acc, PRINTED>(s[q], xs[q], k);
+      rec[q].fg = fg_from<Acc, PRINTED>(rec[q].qd, s[q], xs[q], k);
       mk.v[q] = rec[q].fg ? uint8_t(255) : uint8_t(0);
       cd.v[q] = uint8_t(code_of<Acc>(rec[q]));
       bgv.v[q] = Io(s[q].mA);
@@ -286,8 +286,8 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
     static_cast<Acc*>(a.var_a)[pix + q] = s[q].vA;
     static_cast<Acc*>(a.mean_c)[pix + q] = s[q].mC;
     static_cast<Acc*>(a.var_c)[pix + q] = s[q].vC;
-    a.age_a[pix + q] = uint8_t(s[q].aA);
-    a.age_c[pix + q] = uint8_t(s[q].aC);
+    a.age_a[pix + q] = age_out<Acc>(s[q].aA);
+    a.age_c[pix + q] = age_out<Acc>(s[q].aC);
   }
 }
 

@@ -27,6 +27,13 @@ __device__ __forceinline__ double stored(double v) {
   return __builtin_fmin(255.0, __builtin_fmax(0.0, __builtin_trunc(v)));
 }
 
+// the mask of the step, on the stored values after the exchange
+template <typename Acc, bool PRINTED>
+__device__ __forceinline__ bool fg_of(const Model<Acc>& s, const Acc x, const StepConsts<Acc>& k) {
+  const Acc d = s.mA - x;
+  return fg_from<Acc, PRINTED>(d * d, s, x, k);
+}
+
 template <int P, bool CODES, bool PRINTED>
 __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
   __shared__ TableEntry<double> tbl[TABLE_SIZE];
@@ -57,8 +64,8 @@ __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
       s[q].vA = double(vA.v[q]);
       s[q].mC = double(mC.v[q]);
       s[q].vC = double(vC.v[q]);
-      s[q].aA = aA.v[q];
-      s[q].aC = aC.v[q];
+      s[q].aA = age_in<double>(aA.v[q]);
+      s[q].aC = age_in<double>(aC.v[q]);
     }
   }
 
@@ -68,22 +75,22 @@ __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
   auto do_frame = [&](const Vec<uint8_t, P>& xv, int64_t t) {
     double xs[P];
     StepRecord<double> r[P];
-    bool any = false;
+    uint64_t any = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       xs[q] = double(xv.v[q]);
-      r[q] = step_core<double>(s[q], xs[q], k, tbl);
+      r[q] = step_core<double, false>(s[q], xs[q], k, tbl);
       // the matched model (or the reset candidate) is written to 8-bit storage;
       // the other models hold stored values already, which the rule keeps
       s[q].mA = stored(s[q].mA);
       s[q].vA = stored(s[q].vA);
       s[q].mC = stored(s[q].mC);
       s[q].vC = stored(s[q].vC);
-      any |= r[q].swap;
+      any |= r[q].swap_lanes;
     }
-    if (any_lane(any)) {
+    if (any != 0) {
 #pragma unroll
-      for (int q = 0; q < P; ++q) apply_swap<double>(s[q], xs[q], k, r[q].swap);
+      for (int q = 0; q < P; ++q) exchange<double, false>(s[q], xs[q], k, r[q]);
     }
     Vec<uint8_t, P> mk, cd;
 #pragma unroll
@@ -114,8 +121,8 @@ __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
     vA.v[q] = uint8_t(s[q].vA);
     mC.v[q] = uint8_t(s[q].mC);
     vC.v[q] = uint8_t(s[q].vC);
-    aA.v[q] = uint8_t(s[q].aA);
-    aC.v[q] = uint8_t(s[q].aC);
+    aA.v[q] = age_out<double>(s[q].aA);
+    aC.v[q] = age_out<double>(s[q].aC);
   }
   *reinterpret_cast<Vec<uint8_t, P>*>(static_cast<uint8_t*>(a.mean_a) + pix) = mA;
   *reinterpret_cast<Vec<uint8_t, P>*>(static_cast<uint8_t*>(a.var_a) + pix) = vA;
@@ -174,26 +181,26 @@ u8_step_kernel(const FwdArgs a) {
     Model<double> s[P];
     double xs[P];
     StepRecord<double> r[P];
-    bool any = false;
+    uint64_t any = 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       s[q].mA = double(cur.p[0].v[q]);
       s[q].vA = double(cur.p[1].v[q]);
       s[q].mC = double(cur.p[2].v[q]);
       s[q].vC = double(cur.p[3].v[q]);
-      s[q].aA = cur.aA.v[q];
-      s[q].aC = cur.aC.v[q];
+      s[q].aA = age_in<double>(cur.aA.v[q]);
+      s[q].aC = age_in<double>(cur.aC.v[q]);
       xs[q] = double(cur.x.v[q]);
-      r[q] = step_core<double>(s[q], xs[q], k, tbl);
+      r[q] = step_core<double, false>(s[q], xs[q], k, tbl);
       s[q].mA = stored(s[q].mA);
       s[q].vA = stored(s[q].vA);
       s[q].mC = stored(s[q].mC);
       s[q].vC = stored(s[q].vC);
-      any |= r[q].swap;
+      any |= r[q].swap_lanes;
     }
-    if (any_lane(any)) {
+    if (any != 0) {
 #pragma unroll
-      for (int q = 0; q < P; ++q) apply_swap<double>(s[q], xs[q], k, r[q].swap);
+      for (int q = 0; q < P; ++q) exchange<double, false>(s[q], xs[q], k, r[q]);
     }
     V mk, cd, o[4], oA, oC;
 #pragma unroll
@@ -205,8 +212,8 @@ u8_step_kernel(const FwdArgs a) {
       o[1].v[q] = uint8_t(s[q].vA);
       o[2].v[q] = uint8_t(s[q].mC);
       o[3].v[q] = uint8_t(s[q].vC);
-      oA.v[q] = uint8_t(s[q].aA);
-      oC.v[q] = uint8_t(s[q].aC);
+      oA.v[q] = age_out<double>(s[q].aA);
+      oC.v[q] = age_out<double>(s[q].aC);
     }
     int64_t pix, foff;
     offsets(g, pix, foff);
@@ -337,11 +344,11 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
       s[q].vA = double(planes_in[1][pix + q]);
       s[q].mC = double(planes_in[2][pix + q]);
       s[q].vC = double(planes_in[3][pix + q]);
-      s[q].aA = a.age_a[pix + q];
-      s[q].aC = a.age_c[pix + q];
+      s[q].aA = age_in<double>(a.age_a[pix + q]);
+      s[q].aC = age_in<double>(a.age_c[pix + q]);
     } else {
       s[q].mA = s[q].vA = s[q].mC = s[q].vC = 0.0;
-      s[q].aA = s[q].aC = 1;
+      s[q].aA = s[q].aC = age_in<double>(1);
     }
   }
 
@@ -420,19 +427,19 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
     }
 
     StepRecord<double> r[PX];
-    bool any = false;
+    uint64_t any = 0;
 #pragma unroll
     for (int q = 0; q < PX; ++q) {
-      r[q] = step_core<double>(s[q], xs[q], k, tbl);
+      r[q] = step_core<double, false>(s[q], xs[q], k, tbl);
       s[q].mA = stored(s[q].mA);
       s[q].vA = stored(s[q].vA);
       s[q].mC = stored(s[q].mC);
       s[q].vC = stored(s[q].vC);
-      any |= r[q].swap;
+      any |= r[q].swap_lanes;
     }
-    if (any_lane(any)) {
+    if (any != 0) {
 #pragma unroll
-      for (int q = 0; q < PX; ++q) apply_swap<double>(s[q], xs[q], k, r[q].swap);
+      for (int q = 0; q < PX; ++q) exchange<double, false>(s[q], xs[q], k, r[q]);
     }
     Vec<uint8_t, PX> mk, cd, fv;
 #pragma unroll
@@ -467,8 +474,8 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
     static_cast<uint8_t*>(a.var_a)[pix + q] = uint8_t(s[q].vA);
     static_cast<uint8_t*>(a.mean_c)[pix + q] = uint8_t(s[q].mC);
     static_cast<uint8_t*>(a.var_c)[pix + q] = uint8_t(s[q].vC);
-    a.age_a[pix + q] = uint8_t(s[q].aA);
-    a.age_c[pix + q] = uint8_t(s[q].aC);
+    a.age_a[pix + q] = age_out<double>(s[q].aA);
+    a.age_c[pix + q] = age_out<double>(s[q].aC);
   }
 }
 

@@ -121,17 +121,17 @@ __global__ void __launch_bounds__(256) warp_kernel(const WarpArgs a) {
     s.vA = g[1];
     s.mC = g[2];
     s.vC = g[3];
-    s.aA = age_a;
-    s.aC = age_c;
+    s.aA = age_in<Acc>(age_a);
+    s.aC = age_in<Acc>(age_c);
   } else {
     s.mA = s.mC = x;
     s.vA = s.vC = k.var_init;
-    s.aA = s.aC = 1;
+    s.aA = s.aC = age_in<Acc>(1);
   }
 
   StepRecord<Acc> r = step_core<Acc>(s, x, k, tbl);
-  if (any_lane(r.swap)) apply_swap<Acc>(s, x, k, r.swap);
-  r.fg = a.mask_rule != 0 ? fg_of<Acc, true>(s, x, k) : fg_of<Acc, false>(s, x, k);
+  if (r.swap_lanes != 0) exchange<Acc>(s, x, k, r);
+  r.fg = a.mask_rule != 0 ? fg_from<Acc, true>(r.qd, s, x, k) : fg_from<Acc, false>(r.qd, s, x, k);
 
   a.masks[fo] = r.fg ? uint8_t(255) : uint8_t(0);
   if (a.bg) static_cast<Io*>(a.bg)[fo] = Io(s.mA);
@@ -140,8 +140,8 @@ __global__ void __launch_bounds__(256) warp_kernel(const WarpArgs a) {
   static_cast<Acc*>(a.dst_var_a)[i] = s.vA;
   static_cast<Acc*>(a.dst_mean_c)[i] = s.mC;
   static_cast<Acc*>(a.dst_var_c)[i] = s.vC;
-  a.dst_age_a[i] = uint8_t(s.aA);
-  a.dst_age_c[i] = uint8_t(s.aC);
+  a.dst_age_a[i] = age_out<Acc>(s.aA);
+  a.dst_age_c[i] = age_out<Acc>(s.aC);
 }
 
 template <typename In, typename Acc, typename Io>

@@ -330,6 +330,25 @@ def test_io32_adjoint_is_fp64_rounded_once():
     G.assert_bit_exact("grad_var_init per pixel", px, ref["grad_var_init_px"])
 
 
+@pytest.mark.parametrize("T,K", [(1, 32), (31, 32), (47, 32), (63, 16), (71, 40)])
+def test_io32_adjoint_of_short_chunks(T, K):
+    """Chunks shorter than the 32-frame tape are swept in pieces of 1, 2, 4, 8
+    and 16 frames; lanes beyond the last pixel of the last wavefront stay idle
+    (H*W is no multiple of 64).  Same oracle and bits as above."""
+    H, W, seed = 5, 37, 29
+    p = dsgm.dsgm_params_default(2.0)
+    fr, st = G.device_case(seed, T, H, W, torch.float32, torch.float64)
+    out = dsgm.forward(fr, st, p, bg=True, codes=True, ckpt_every=K, acc=dsgm.ACC_F64_IO32)
+    gbg, gst = _grads(seed + 100, T, H, W, torch.float32)
+    r = dsgm.backward(fr, p, out["ckpt"], K, dsgm.ACC_F64_IO32, gbg, gst)
+    torch.cuda.synchronize()
+    ref = _oracle_bwd(seed, T, H, W, torch.float32, torch.float64, p, out["codes"], gbg, gst)
+    G.assert_bit_exact("grad_frames", r["grad_frames"].cpu().numpy().reshape(T, -1),
+                       ref["grad_frames"].astype(np.float32))
+    px = r["workspace"][: H * W * 8].view(torch.float64).cpu().numpy()
+    G.assert_bit_exact("grad_var_init per pixel", px, ref["grad_var_init_px"])
+
+
 @pytest.mark.slow
 def test_full_size_io32_forward_and_adjoint_sampled():
     """The largest single instance: 2160 x 3840 pixels x 1344 frames (11.1 G
