@@ -49,7 +49,7 @@ bwd_kernel(const BwdArgs a) {
 
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= a.H * a.W) return;
-  const int64_t h = g / a.W;
+  const int64_t h = int64_t(uint32_t(g) / uint32_t(a.W));  // < 2^31 pixels (host check)
   const int64_t w = g - h * a.W;
   const uint32_t foff = uint32_t(h * a.row_stride + w);  // < 2^31 elements (host check)
   const uint32_t off_in = foff * uint32_t(sizeof(In));

@@ -6,8 +6,8 @@
 // also limited to [0, 255], where the conversion has no defined result).  The
 // tests, the swap and the mask then see the stored values.  This kernel runs
 // that model time-fused like fwd_kernel: one lane owns P adjacent pixels of a
-// row for all T frames with their models in registers (as doubles holding the
-// stored integers), and per frame reads P frame bytes and writes P mask bytes.
+// row for all T frames with their models in registers (as the stored
+// integers), and per frame reads P frame bytes and writes P mask bytes.
 // The state is 6 bytes per pixel instead of 68, which is what a T = 1
 // streaming caller moves per frame; such calls run u8_step_kernel below.
 #include "dsgm_ext.h"
@@ -27,80 +27,263 @@ __device__ __forceinline__ double stored(double v) {
   return __builtin_fmin(255.0, __builtin_fmax(0.0, __builtin_trunc(v)));
 }
 
-// the mask of the step, on the stored values after the exchange
-template <typename Acc, bool PRINTED>
-__device__ __forceinline__ bool fg_of(const Model<Acc>& s, const Acc x, const StepConsts<Acc>& k) {
-  const Acc d = s.mA - x;
-  return fg_from<Acc, PRINTED>(d * d, s, x, k);
+// One pixel's models as the integers the images hold, with the thresholds of
+// their match tests; ages are table offsets (age_in<double>).
+struct Model8 {
+  uint32_t mA, vA, tA, mC, vC, tC;
+  int aA, aC;
+};
+
+// The step's tables.  All squared distances of 8-bit values are integers up to
+// 65025, so each double-precision test is an integer comparison with the
+// number of distances that pass it:
+//   match       q < max(ts*v, ts*vf)          <=>  q < match[v]
+//   background  q <= max(td*ref, td*mf)       <=>  q < back[ref]
+// (two comparisons of the real-valued step are one with the larger threshold;
+// fmax drops a NaN, and a NaN threshold passes nothing, as the comparisons do).
+struct Tables8 {
+  TableEntry<double> e[TABLE_SIZE];
+  uint32_t match[256], back[256];
+};
+
+__device__ __forceinline__ uint32_t passing(double n) {
+  return n > 0.0 ? uint32_t(__builtin_fmin(n, 65026.0)) : 0u;  // NaN: 0
+}
+
+// fills the tables and ends with a barrier
+__device__ __forceinline__ void fill_tables(Tables8& t, const StepConsts<double>& k,
+                                            int weight_rule, int age_max, double var_init) {
+  for (int v = threadIdx.x; v < 256; v += blockDim.x) {
+    t.match[v] = passing(__builtin_ceil(__builtin_fmax(k.theta_s * double(v), k.ts_vf)));
+    t.back[v] = passing(__builtin_floor(__builtin_fmax(k.theta_d * double(v), k.td_mf)) + 1.0);
+  }
+  fill_table<double>(t.e, weight_rule, age_max, var_init);
+}
+
+// What a step decided (masks of lanes).
+struct Record8 {
+  uint64_t hit_a, swap;
+  bool hit_c;  // of the lanes whose A failed
+};
+
+// Match tests and update of the matched model (or the reset of C) for one frame
+// of one pixel, on the stored integers; the exchange is left to exchange8().
+// The tests are integer comparisons; the blends are evaluated in double
+// precision in the order of the real-valued step, and each result is written
+// back by dropping its fraction.  A blended mean lies in [0, 255] and a
+// blended variance is not negative (the weights are not, and sum to 1 within a
+// rounding), so the conversion itself is the storage rule but for the
+// variance's upper limit.  Values move under lane masks (update_in_place says
+// why).  CARRY: the new variance's threshold is looked up and kept.  Bound by
+// vector issue; one 1920 x 2560 frame per call took 20.0 us with the
+// real-valued step and the storage rule on all four values, 17.4 us with this
+// one, and 15.9 us with 32-bit lane-group divisions.
+template <bool CARRY>
+__device__ __forceinline__ Record8 step8(Model8& s, const uint32_t x, const uint32_t var_init,
+                                         const Tables8& t) {
+  const int dA = int(x) - int(s.mA), dC = int(x) - int(s.mC);
+  Record8 r;
+  r.hit_a = __builtin_amdgcn_ballot_w64(uint32_t(__mul24(dA, dA)) < s.tA);
+  const bool hitC = uint32_t(__mul24(dC, dC)) < s.tC;
+  int idx = hitC ? s.aC : reset_age<double>();
+  uint32_t m = s.mC, v = s.vC;
+  uint64_t all;
+  asm("s_mov_b64 %[all], exec\n\t"
+      "s_mov_b64 exec, %[h]\n\t"
+      "v_mov_b32 %[i], %[aA]\n\t"
+      "v_mov_b32 %[m], %[mA]\n\t"
+      "v_mov_b32 %[v], %[vA]\n\t"
+      "s_mov_b64 exec, %[all]"
+      : [i] "+v"(idx), [m] "+v"(m), [v] "+v"(v), [all] "=&s"(all)
+      : [aA] "v"(s.aA), [mA] "v"(s.mA), [vA] "v"(s.vA), [h] "s"(r.hit_a));
+  const TableEntry<double>& e = *reinterpret_cast<const TableEntry<double>*>(
+      reinterpret_cast<const char*>(t.e) + idx);
+  const double u = e.u, w = e.w, xd = double(x);
+  const int next = e.next;
+  const double mn = blend(u, double(m), w, xd);
+  const double d = mn - xd;
+  const uint32_t vb = uint32_t(blend(u, double(v), w, d * d));
+  const uint32_t mi = uint32_t(mn);
+  uint32_t vi = vb < 255u ? vb : 255u;
+  vi = idx == reset_age<double>() ? var_init : vi;  // a reset: (x, var_init, 1)
+  if constexpr (CARRY) {
+    const uint32_t tn = t.match[vi];
+    asm("s_mov_b64 %[all], exec\n\t"
+        "s_mov_b64 exec, %[h]\n\t"
+        "v_mov_b32 %[mA], %[m]\n\t"
+        "v_mov_b32 %[vA], %[v]\n\t"
+        "v_mov_b32 %[tA], %[t]\n\t"
+        "v_mov_b32 %[aA], %[n]\n\t"
+        "s_andn2_b64 exec, %[all], %[h]\n\t"
+        "v_mov_b32 %[mC], %[m]\n\t"
+        "v_mov_b32 %[vC], %[v]\n\t"
+        "v_mov_b32 %[tC], %[t]\n\t"
+        "v_mov_b32 %[aC], %[n]\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [tA] "+v"(s.tA), [aA] "+v"(s.aA), [mC] "+v"(s.mC),
+          [vC] "+v"(s.vC), [tC] "+v"(s.tC), [aC] "+v"(s.aC), [all] "=&s"(all)
+        : [m] "v"(mi), [v] "v"(vi), [t] "v"(tn), [n] "v"(next), [h] "s"(r.hit_a)
+        : "scc");
+  } else {
+    asm("s_mov_b64 %[all], exec\n\t"
+        "s_mov_b64 exec, %[h]\n\t"
+        "v_mov_b32 %[mA], %[m]\n\t"
+        "v_mov_b32 %[vA], %[v]\n\t"
+        "v_mov_b32 %[aA], %[n]\n\t"
+        "s_andn2_b64 exec, %[all], %[h]\n\t"
+        "v_mov_b32 %[mC], %[m]\n\t"
+        "v_mov_b32 %[vC], %[v]\n\t"
+        "v_mov_b32 %[aC], %[n]\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [aA] "+v"(s.aA), [mC] "+v"(s.mC), [vC] "+v"(s.vC),
+          [aC] "+v"(s.aC), [all] "=&s"(all)
+        : [m] "v"(mi), [v] "v"(vi), [n] "v"(next), [h] "s"(r.hit_a)
+        : "scc");
+  }
+  r.hit_c = hitC && !__builtin_amdgcn_inverse_ballot_w64(r.hit_a);
+  r.swap = __builtin_amdgcn_ballot_w64(s.aC > s.aA);
+  return r;
+}
+
+// the exchange in the lanes of `swap`: A <- C, C <- (x, var_init, 1)
+template <bool CARRY>
+__device__ __forceinline__ void exchange8(Model8& s, const uint32_t x, const uint32_t var_init,
+                                          const uint64_t swap, const Tables8& t) {
+  const uint32_t ti = CARRY ? t.match[var_init] : 0u;
+  uint64_t all;
+  asm("s_mov_b64 %[all], exec\n\t"
+      "s_mov_b64 exec, %[h]\n\t"
+      "v_mov_b32 %[mA], %[mC]\n\t"
+      "v_mov_b32 %[vA], %[vC]\n\t"
+      "v_mov_b32 %[tA], %[tC]\n\t"
+      "v_mov_b32 %[aA], %[aC]\n\t"
+      "v_mov_b32 %[mC], %[x]\n\t"
+      "v_mov_b32 %[vC], %[v]\n\t"
+      "v_mov_b32 %[tC], %[t]\n\t"
+      "v_mov_b32 %[aC], %[one]\n\t"
+      "s_mov_b64 exec, %[all]"
+      : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [tA] "+v"(s.tA), [aA] "+v"(s.aA), [mC] "+v"(s.mC),
+        [vC] "+v"(s.vC), [tC] "+v"(s.tC), [aC] "+v"(s.aC), [all] "=&s"(all)
+      : [x] "v"(x), [v] "v"(var_init), [t] "v"(ti), [h] "s"(swap),
+        [one] "n"(int(sizeof(TableEntry<double>))));
+}
+
+// The frame of a lane's P pixels: steps, exchanges and background tests; the
+// mask bytes, and with CODES the decision codes.
+template <int P, bool CARRY, bool CODES, bool PRINTED>
+__device__ __forceinline__ uint32_t frame8(Model8 (&s)[P], const uint32_t (&x)[P],
+                                           const uint32_t var_init, const Tables8& t,
+                                           Vec<uint8_t, P>& codes) {
+  Record8 r[P];
+  uint64_t any = 0, back[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    r[q] = step8<CARRY>(s[q], x[q], var_init, t);
+    any |= r[q].swap;
+  }
+  if (any != 0) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) exchange8<CARRY>(s[q], x[q], var_init, r[q].swap, t);
+  }
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const int d = int(x[q]) - int(s[q].mA);
+    const bool b = uint32_t(__mul24(d, d)) < t.back[PRINTED ? x[q] : s[q].vA];
+    back[q] = __builtin_amdgcn_ballot_w64(b);
+    if (CODES) {
+      const bool hitA = __builtin_amdgcn_inverse_ballot_w64(r[q].hit_a);
+      codes.v[q] = uint8_t((hitA ? CODE_HIT_A : (r[q].hit_c ? CODE_HIT_C : CODE_RESET)) |
+                           (__builtin_amdgcn_inverse_ballot_w64(r[q].swap) ? CODE_SWAP : 0u) |
+                           (b ? 0u : CODE_FG));
+    }
+  }
+  return mask_bytes<P>(back);
+}
+
+// P bytes of each state plane <-> a lane's models
+template <int P>
+struct Planes8 {
+  Vec<uint8_t, P> mA, vA, mC, vC, aA, aC;
+};
+template <int P>
+__device__ __forceinline__ void unpack8(const Planes8<P>& b, const Tables8& t, Model8 (&s)[P]) {
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    s[q].mA = b.mA.v[q];
+    s[q].vA = b.vA.v[q];
+    s[q].mC = b.mC.v[q];
+    s[q].vC = b.vC.v[q];
+    s[q].aA = age_in<double>(b.aA.v[q]);
+    s[q].aC = age_in<double>(b.aC.v[q]);
+    s[q].tA = t.match[s[q].vA];
+    s[q].tC = t.match[s[q].vC];
+  }
+}
+template <int P>
+__device__ __forceinline__ Planes8<P> pack8(const Model8 (&s)[P]) {
+  Planes8<P> b;
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    b.mA.v[q] = uint8_t(s[q].mA);
+    b.vA.v[q] = uint8_t(s[q].vA);
+    b.mC.v[q] = uint8_t(s[q].mC);
+    b.vC.v[q] = uint8_t(s[q].vC);
+    b.aA.v[q] = age_out<double>(s[q].aA);
+    b.aC.v[q] = age_out<double>(s[q].aC);
+  }
+  return b;
+}
+template <int P>
+__device__ __forceinline__ Planes8<P> load8(const FwdArgs& a, int64_t pix) {
+  using V = Vec<uint8_t, P>;
+  Planes8<P> b;
+  b.mA = *reinterpret_cast<const V*>(static_cast<const uint8_t*>(a.mean_a) + pix);
+  b.vA = *reinterpret_cast<const V*>(static_cast<const uint8_t*>(a.var_a) + pix);
+  b.mC = *reinterpret_cast<const V*>(static_cast<const uint8_t*>(a.mean_c) + pix);
+  b.vC = *reinterpret_cast<const V*>(static_cast<const uint8_t*>(a.var_c) + pix);
+  b.aA = *reinterpret_cast<const V*>(a.age_a + pix);
+  b.aC = *reinterpret_cast<const V*>(a.age_c + pix);
+  return b;
+}
+template <int P>
+__device__ __forceinline__ void store8(const FwdArgs& a, int64_t pix, const Planes8<P>& b) {
+  using V = Vec<uint8_t, P>;
+  *reinterpret_cast<V*>(static_cast<uint8_t*>(a.mean_a) + pix) = b.mA;
+  *reinterpret_cast<V*>(static_cast<uint8_t*>(a.var_a) + pix) = b.vA;
+  *reinterpret_cast<V*>(static_cast<uint8_t*>(a.mean_c) + pix) = b.mC;
+  *reinterpret_cast<V*>(static_cast<uint8_t*>(a.var_c) + pix) = b.vC;
+  *reinterpret_cast<V*>(a.age_a + pix) = b.aA;
+  *reinterpret_cast<V*>(a.age_c + pix) = b.aC;
 }
 
 template <int P, bool CODES, bool PRINTED>
 __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
-  __shared__ TableEntry<double> tbl[TABLE_SIZE];
-  fill_table<double>(tbl, a.weight_rule, a.age_max, a.var_init);  // var_init already stored
+  __shared__ Tables8 tbl;
   const StepConsts<double> k =
       make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
+  fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // var_init already stored
+  const uint32_t var_init = uint32_t(a.var_init);
 
   const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= a.ngroups) return;  // no barrier follows
   const geom::Group G = geom::group_of(g, a.groups_per_row, P, a.W, a.row_stride);
   const int64_t pix = G.soff, foff = G.foff;
 
-  Model<double> s[P];
-  {
-    const Vec<uint8_t, P> mA = *reinterpret_cast<const Vec<uint8_t, P>*>(
-        static_cast<const uint8_t*>(a.mean_a) + pix);
-    const Vec<uint8_t, P> vA = *reinterpret_cast<const Vec<uint8_t, P>*>(
-        static_cast<const uint8_t*>(a.var_a) + pix);
-    const Vec<uint8_t, P> mC = *reinterpret_cast<const Vec<uint8_t, P>*>(
-        static_cast<const uint8_t*>(a.mean_c) + pix);
-    const Vec<uint8_t, P> vC = *reinterpret_cast<const Vec<uint8_t, P>*>(
-        static_cast<const uint8_t*>(a.var_c) + pix);
-    const Vec<uint8_t, P> aA = *reinterpret_cast<const Vec<uint8_t, P>*>(a.age_a + pix);
-    const Vec<uint8_t, P> aC = *reinterpret_cast<const Vec<uint8_t, P>*>(a.age_c + pix);
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      s[q].mA = double(mA.v[q]);
-      s[q].vA = double(vA.v[q]);
-      s[q].mC = double(mC.v[q]);
-      s[q].vC = double(vC.v[q]);
-      s[q].aA = age_in<double>(aA.v[q]);
-      s[q].aC = age_in<double>(aC.v[q]);
-    }
-  }
+  Model8 s[P];
+  unpack8<P>(load8<P>(a, pix), tbl, s);
 
   const uint8_t* frames = static_cast<const uint8_t*>(a.frames);
   constexpr int U = 8;  // frames in flight
   auto frame_at = [&](int64_t t) { return ld_stream<uint8_t, P>(frames + t * a.frame_stride + foff); };
   auto do_frame = [&](const Vec<uint8_t, P>& xv, int64_t t) {
-    double xs[P];
-    StepRecord<double> r[P];
-    uint64_t any = 0;
+    uint32_t xs[P];
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-      xs[q] = double(xv.v[q]);
-      r[q] = step_core<double, false>(s[q], xs[q], k, tbl);
-      // the matched model (or the reset candidate) is written to 8-bit storage;
-      // the other models hold stored values already, which the rule keeps
-      s[q].mA = stored(s[q].mA);
-      s[q].vA = stored(s[q].vA);
-      s[q].mC = stored(s[q].mC);
-      s[q].vC = stored(s[q].vC);
-      any |= r[q].swap_lanes;
-    }
-    if (any != 0) {
-#pragma unroll
-      for (int q = 0; q < P; ++q) exchange<double, false>(s[q], xs[q], k, r[q]);
-    }
-    Vec<uint8_t, P> mk, cd;
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      r[q].fg = fg_of<double, PRINTED>(s[q], xs[q], k);
-      mk.v[q] = r[q].fg ? uint8_t(255) : uint8_t(0);
-      cd.v[q] = uint8_t(code_of<double>(r[q]));
-    }
+    for (int q = 0; q < P; ++q) xs[q] = xv.v[q];
+    Vec<uint8_t, P> cd;
+    const auto mk = typename fwd::Raw<P>::type(
+        frame8<P, true, CODES, PRINTED>(s, xs, var_init, tbl, cd));
     const int64_t o = t * a.frame_stride + foff;
-    st_stream<uint8_t, P>(a.masks + o, mk);
+    st_stream<uint8_t, P>(a.masks + o, __builtin_bit_cast(Vec<uint8_t, P>, mk));
     if (CODES) *reinterpret_cast<Vec<uint8_t, P>*>(a.codes + o) = cd;
   };
   const int64_t T = a.T;
@@ -113,23 +296,7 @@ __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
     for (int u = 0; u < U; ++u) do_frame(xb[u], t + u);
   }
   for (; t < T; ++t) do_frame(frame_at(t), t);
-
-  Vec<uint8_t, P> mA, vA, mC, vC, aA, aC;
-#pragma unroll
-  for (int q = 0; q < P; ++q) {
-    mA.v[q] = uint8_t(s[q].mA);
-    vA.v[q] = uint8_t(s[q].vA);
-    mC.v[q] = uint8_t(s[q].mC);
-    vC.v[q] = uint8_t(s[q].vC);
-    aA.v[q] = age_out<double>(s[q].aA);
-    aC.v[q] = age_out<double>(s[q].aC);
-  }
-  *reinterpret_cast<Vec<uint8_t, P>*>(static_cast<uint8_t*>(a.mean_a) + pix) = mA;
-  *reinterpret_cast<Vec<uint8_t, P>*>(static_cast<uint8_t*>(a.var_a) + pix) = vA;
-  *reinterpret_cast<Vec<uint8_t, P>*>(static_cast<uint8_t*>(a.mean_c) + pix) = mC;
-  *reinterpret_cast<Vec<uint8_t, P>*>(static_cast<uint8_t*>(a.var_c) + pix) = vC;
-  *reinterpret_cast<Vec<uint8_t, P>*>(a.age_a + pix) = aA;
-  *reinterpret_cast<Vec<uint8_t, P>*>(a.age_c + pix) = aC;
+  store8<P>(a, pix, pack8<P>(s));
 }
 
 // One frame per call (T = 1, the streaming step): a persistent grid whose
@@ -142,94 +309,55 @@ __global__ void __launch_bounds__(256) u8_kernel(const FwdArgs a) {
 template <int P, bool CODES, bool PRINTED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 u8_step_kernel(const FwdArgs a) {
-  __shared__ TableEntry<double> tbl[TABLE_SIZE];
+  __shared__ Tables8 tbl;
   using V = Vec<uint8_t, P>;
   const uint8_t* frame = static_cast<const uint8_t*>(a.frames);
-  uint8_t* const planes[4] = {static_cast<uint8_t*>(a.mean_a), static_cast<uint8_t*>(a.var_a),
-                              static_cast<uint8_t*>(a.mean_c), static_cast<uint8_t*>(a.var_c)};
   struct Bytes {
-    V x, p[4], aA, aC;
+    V x;
+    Planes8<P> p;
+    uint32_t pix, foff;  // < 2^31 (host check)
   };
   // group g: row h, first column w (pixel index h*W + w, frame offset h*row_stride + w)
-  auto offsets = [&](int64_t g, int64_t& pix, int64_t& foff) {
-    const geom::Group G = geom::group_of(g, a.groups_per_row, P, a.W, a.row_stride);
-    pix = G.soff;
-    foff = G.foff;
-  };
   auto load = [&](int64_t g, Bytes& b) {
-    int64_t pix, foff;
-    offsets(g, pix, foff);
-    b.x = ld_stream<uint8_t, P>(frame + foff);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b.p[i] = *reinterpret_cast<const V*>(planes[i] + pix);
-    b.aA = *reinterpret_cast<const V*>(a.age_a + pix);
-    b.aC = *reinterpret_cast<const V*>(a.age_c + pix);
+    const geom::Group G = geom::group_of(g, a.groups_per_row, P, a.W, a.row_stride);
+    b.pix = uint32_t(G.soff);
+    b.foff = uint32_t(G.foff);
+    b.x = ld_stream<uint8_t, P>(frame + b.foff);
+    b.p = load8<P>(a, b.pix);
   };
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   Bytes cur, nxt;
-  // the first group's bytes are requested before the table is built, so their
+  // the first group's bytes are requested before the tables are built, so their
   // latency overlaps the table's divisions and its barrier
   if (g < a.ngroups) load(g, cur);
-  fill_table<double>(tbl, a.weight_rule, a.age_max, a.var_init);
   const StepConsts<double> k =
       make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
+  fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);
+  const uint32_t var_init = uint32_t(a.var_init);
   if (g >= a.ngroups) return;  // no barrier follows
   for (; g < a.ngroups; g += stride) {
     const bool more = g + stride < a.ngroups;
     if (more) load(g + stride, nxt);
-    Model<double> s[P];
-    double xs[P];
-    StepRecord<double> r[P];
-    uint64_t any = 0;
+    Model8 s[P];
+    uint32_t xs[P];
+    unpack8<P>(cur.p, tbl, s);
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-      s[q].mA = double(cur.p[0].v[q]);
-      s[q].vA = double(cur.p[1].v[q]);
-      s[q].mC = double(cur.p[2].v[q]);
-      s[q].vC = double(cur.p[3].v[q]);
-      s[q].aA = age_in<double>(cur.aA.v[q]);
-      s[q].aC = age_in<double>(cur.aC.v[q]);
-      xs[q] = double(cur.x.v[q]);
-      r[q] = step_core<double, false>(s[q], xs[q], k, tbl);
-      s[q].mA = stored(s[q].mA);
-      s[q].vA = stored(s[q].vA);
-      s[q].mC = stored(s[q].mC);
-      s[q].vC = stored(s[q].vC);
-      any |= r[q].swap_lanes;
-    }
-    if (any != 0) {
-#pragma unroll
-      for (int q = 0; q < P; ++q) exchange<double, false>(s[q], xs[q], k, r[q]);
-    }
-    V mk, cd, o[4], oA, oC;
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      r[q].fg = fg_of<double, PRINTED>(s[q], xs[q], k);
-      mk.v[q] = r[q].fg ? uint8_t(255) : uint8_t(0);
-      cd.v[q] = uint8_t(code_of<double>(r[q]));
-      o[0].v[q] = uint8_t(s[q].mA);
-      o[1].v[q] = uint8_t(s[q].vA);
-      o[2].v[q] = uint8_t(s[q].mC);
-      o[3].v[q] = uint8_t(s[q].vC);
-      oA.v[q] = age_out<double>(s[q].aA);
-      oC.v[q] = age_out<double>(s[q].aC);
-    }
-    int64_t pix, foff;
-    offsets(g, pix, foff);
-    st_stream<uint8_t, P>(a.masks + foff, mk);
-    if (CODES) *reinterpret_cast<V*>(a.codes + foff) = cd;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<V*>(planes[i] + pix) = o[i];
-    *reinterpret_cast<V*>(a.age_a + pix) = oA;
-    *reinterpret_cast<V*>(a.age_c + pix) = oC;
+    for (int q = 0; q < P; ++q) xs[q] = cur.x.v[q];
+    V cd;
+    const auto mk = typename fwd::Raw<P>::type(
+        frame8<P, false, CODES, PRINTED>(s, xs, var_init, tbl, cd));
+    st_stream<uint8_t, P>(a.masks + cur.foff, __builtin_bit_cast(V, mk));
+    if (CODES) *reinterpret_cast<V*>(a.codes + cur.foff) = cd;
+    store8<P>(a, cur.pix, pack8<P>(s));
     if (more) cur = nxt;
   }
 }
 
 // persistent grid of the one-frame kernel: four 256-lane workgroups per CU
-// (measured against eight and sixteen on 1920 x 2560 frames: 22.1 us per
-// frame against 22.7 and 23.2; a grid of one group per lane took 23.7)
+// (measured against eight and sixteen on 1920 x 2560 frames, with the
+// real-valued step: 22.1 us per frame against 22.7 and 23.2; a grid of one group
+// per lane took 23.7)
 constexpr int64_t kStepGrid = 1024;
 
 template <int P, bool CODES, bool PRINTED>
@@ -292,10 +420,11 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
   constexpr int N = 2 * RG + 1;  // taps per window row
   __shared__ float buf_raw[G::RAW_N];
   __shared__ float buf_gb[RG > 0 ? G::GB_N : 1];
-  __shared__ TableEntry<double> tbl[TABLE_SIZE];
-  fill_table<double>(tbl, a.weight_rule, a.age_max, a.var_init);  // var_init already stored
+  __shared__ Tables8 tbl;
   const StepConsts<double> k =
       make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
+  fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // var_init already stored
+  const uint32_t var_init = uint32_t(a.var_init);
   float w2[N * N];  // the window's weights, row-major, rounded once
 #pragma unroll
   for (int i = 0; i < N; ++i)
@@ -336,20 +465,19 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
                                        static_cast<const uint8_t*>(a.var_a),
                                        static_cast<const uint8_t*>(a.mean_c),
                                        static_cast<const uint8_t*>(a.var_c)};
-  Model<double> s[PX];
+  Model8 s[PX];
+  {
+    Planes8<PX> b;
 #pragma unroll
-  for (int q = 0; q < PX; ++q) {
-    if (valid[q]) {
-      s[q].mA = double(planes_in[0][pix + q]);
-      s[q].vA = double(planes_in[1][pix + q]);
-      s[q].mC = double(planes_in[2][pix + q]);
-      s[q].vC = double(planes_in[3][pix + q]);
-      s[q].aA = age_in<double>(a.age_a[pix + q]);
-      s[q].aC = age_in<double>(a.age_c[pix + q]);
-    } else {
-      s[q].mA = s[q].vA = s[q].mC = s[q].vC = 0.0;
-      s[q].aA = s[q].aC = age_in<double>(1);
+    for (int q = 0; q < PX; ++q) {
+      b.mA.v[q] = valid[q] ? planes_in[0][pix + q] : uint8_t(0);
+      b.vA.v[q] = valid[q] ? planes_in[1][pix + q] : uint8_t(0);
+      b.mC.v[q] = valid[q] ? planes_in[2][pix + q] : uint8_t(0);
+      b.vC.v[q] = valid[q] ? planes_in[3][pix + q] : uint8_t(0);
+      b.aA.v[q] = valid[q] ? a.age_a[pix + q] : uint8_t(1);
+      b.aC.v[q] = valid[q] ? a.age_c[pix + q] : uint8_t(1);
     }
+    unpack8<PX>(b, tbl, s);
   }
 
   const uint8_t* frames = static_cast<const uint8_t*>(a.frames);
@@ -398,7 +526,7 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 
     // 3. each pixel's median of the nine blurred bytes (exact in single
     // precision: the values are integers), then the 8-bit update
-    double xs[PX];
+    uint32_t xs[PX];
     if constexpr (MED) {
       float lo[PX + 2], md[PX + 2], hi[PX + 2];
 #pragma unroll
@@ -418,37 +546,23 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
         const float b0 = __builtin_fmaxf(__builtin_fminf(md[q], md[q + 1]),
                                          __builtin_fminf(__builtin_fmaxf(md[q], md[q + 1]), md[q + 2]));
         const float c0 = __builtin_fminf(__builtin_fminf(hi[q], hi[q + 1]), hi[q + 2]);
-        xs[q] = double(__builtin_fmaxf(__builtin_fminf(a0, b0),
+        xs[q] = uint32_t(__builtin_fmaxf(__builtin_fminf(a0, b0),
                                        __builtin_fminf(__builtin_fmaxf(a0, b0), c0)));
       }
     } else {
 #pragma unroll
-      for (int q = 0; q < PX; ++q) xs[q] = double(gbp[gr[1] * GW + gc[q + 1]]);
+      for (int q = 0; q < PX; ++q) xs[q] = uint32_t(gbp[gr[1] * GW + gc[q + 1]]);
     }
 
-    StepRecord<double> r[PX];
-    uint64_t any = 0;
-#pragma unroll
-    for (int q = 0; q < PX; ++q) {
-      r[q] = step_core<double, false>(s[q], xs[q], k, tbl);
-      s[q].mA = stored(s[q].mA);
-      s[q].vA = stored(s[q].vA);
-      s[q].mC = stored(s[q].mC);
-      s[q].vC = stored(s[q].vC);
-      any |= r[q].swap_lanes;
-    }
-    if (any != 0) {
-#pragma unroll
-      for (int q = 0; q < PX; ++q) exchange<double, false>(s[q], xs[q], k, r[q]);
-    }
     Vec<uint8_t, PX> mk, cd, fv;
+    if (a.codes)
+      mk = __builtin_bit_cast(decltype(mk),
+                              frame8<PX, true, true, PRINTED>(s, xs, var_init, tbl, cd));
+    else
+      mk = __builtin_bit_cast(decltype(mk),
+                              frame8<PX, true, false, PRINTED>(s, xs, var_init, tbl, cd));
 #pragma unroll
-    for (int q = 0; q < PX; ++q) {
-      r[q].fg = fg_of<double, PRINTED>(s[q], xs[q], k);
-      mk.v[q] = r[q].fg ? uint8_t(255) : uint8_t(0);
-      cd.v[q] = uint8_t(code_of<double>(r[q]));
-      fv.v[q] = uint8_t(xs[q]);
-    }
+    for (int q = 0; q < PX; ++q) fv.v[q] = uint8_t(xs[q]);
     uint8_t* const filt = static_cast<uint8_t*>(a.filtered);
     const int64_t o = t * a.frame_stride + foff;
     if (vec_ok) {
@@ -470,12 +584,13 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 #pragma unroll
   for (int q = 0; q < PX; ++q) {
     if (!valid[q]) continue;
-    static_cast<uint8_t*>(a.mean_a)[pix + q] = uint8_t(s[q].mA);
-    static_cast<uint8_t*>(a.var_a)[pix + q] = uint8_t(s[q].vA);
-    static_cast<uint8_t*>(a.mean_c)[pix + q] = uint8_t(s[q].mC);
-    static_cast<uint8_t*>(a.var_c)[pix + q] = uint8_t(s[q].vC);
-    a.age_a[pix + q] = age_out<double>(s[q].aA);
-    a.age_c[pix + q] = age_out<double>(s[q].aC);
+    const Planes8<PX> b = pack8<PX>(s);
+    static_cast<uint8_t*>(a.mean_a)[pix + q] = b.mA.v[q];
+    static_cast<uint8_t*>(a.var_a)[pix + q] = b.vA.v[q];
+    static_cast<uint8_t*>(a.mean_c)[pix + q] = b.mC.v[q];
+    static_cast<uint8_t*>(a.var_c)[pix + q] = b.vC.v[q];
+    a.age_a[pix + q] = b.aA.v[q];
+    a.age_c[pix + q] = b.aC.v[q];
   }
 }
 

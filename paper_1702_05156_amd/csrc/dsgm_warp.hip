@@ -56,7 +56,8 @@ __global__ void __launch_bounds__(256) warp_kernel(const WarpArgs a) {
   // that neighbouring output rows share
   const int64_t i = tile_of(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
   const bool active = i < a.H * a.W;
-  const int64_t y = active ? i / a.W : 0, c = active ? i - y * a.W : 0;
+  const int64_t y = active ? int64_t(uint32_t(i) / uint32_t(a.W)) : 0,  // < 2^31 pixels
+                c = active ? i - y * a.W : 0;
   const int64_t fo = y * a.row_stride + c;  // frame / output offset
 
   // The frame value, the source position (dsgm_geom.h) and the gathers are

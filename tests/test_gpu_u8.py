@@ -51,6 +51,38 @@ def test_u8_forward_bit_exact(wr, mr, T, H, W):
         G.assert_bit_exact(k, got.astype(np.int64), ref[k].astype(np.int64))
 
 
+@pytest.mark.parametrize("theta_s,theta_d,var_floor,mask_floor,age_max", [
+    (0.0, 0.0, 0.0, 0.0, 30),                 # nothing matches, only equality is background
+    (1.0 / 3.0, 7.1, 0.7, -3.0, 255),         # products that round; a floor below zero
+    (254.99609375, 1e300, 1e-300, 255.0, 1),  # thresholds at and beyond the largest distance
+    (float("inf"), float("inf"), 0.0, 0.0, 2),  # inf * 0 is NaN: passes nothing
+])
+@pytest.mark.parametrize("mr", [0, 1])
+def test_u8_integer_thresholds(theta_s, theta_d, var_floor, mask_floor, age_max, mr):
+    """The tests are integer comparisons against per-launch tables: parameters
+    where a threshold is zero, negative, fractional, beyond every distance or
+    NaN give the double-precision comparisons' decisions."""
+    T, H, W = 30, 9, 52
+    x, st = _case(91, T, H, W)
+    st["age_a"], st["age_c"] = (np.minimum(st[k], age_max).astype(np.uint8) for k in ("age_a", "age_c"))
+    p = _params(0, mr)
+    p.theta_s, p.theta_d, p.var_floor, p.mask_floor, p.age_max = (theta_s, theta_d, var_floor,
+                                                                 mask_floor, age_max)
+    dst = _dev_state(st, H, W)
+    out = dsgm.forward(torch.as_tensor(x, device="cuda"), dst, p, codes=True)
+    one = _dev_state(st, H, W)
+    m1 = torch.cat([dsgm.forward(torch.as_tensor(x[t:t + 1], device="cuda"), one, p)["masks"]
+                    for t in range(T)])
+    torch.cuda.synchronize()
+    ref = oracle.forward_u8(x.reshape(T, -1), st, G.oracle_params(p))
+    G.assert_bit_exact("codes", G.flat(out["codes"]).astype(np.uint8), ref["codes"])
+    G.assert_bit_exact("one-frame masks", G.flat(m1).astype(np.uint8), ref["masks"])
+    for k in ("mean_a", "var_a", "mean_c", "var_c", "age_a", "age_c"):
+        for d in (dst, one):
+            G.assert_bit_exact(k, getattr(d, k).cpu().numpy().ravel().astype(np.int64),
+                               ref[k].astype(np.int64))
+
+
 def test_u8_streaming_equals_fused_and_no_codes_path():
     T, H, W = 40, 16, 128
     x, st = _case(75, T, H, W)
