@@ -167,6 +167,23 @@ int preferred_vector(int in_dtype, int acc) {
   return 2;
 }
 
+// Pixels per lane, at most P, at which a frame of px pixels still gives every
+// SIMD of the 256 CUs enough wavefronts.  A wavefront's frames are a serial
+// chain, so with fewer than about three per SIMD (two with double state, whose
+// instructions take longer to issue) the chain's latency bounds the call, and
+// narrower lanes, of which there are more, are faster although they issue more
+// loads and stores.  Measured, pixels per lane 4 / 2 / 1: BF16 frames with FP32
+// state 500 x 240 x 320: 216 / 137 / 104 us, 200 x 480 x 640: 97 / 70 / 65 us,
+// 100 x 720 x 1280 (3,600 wavefronts at 4): 75 / 75 / 83 us; 8-bit 200 x 240 x
+// 320: 119 / 71 / 50 us; FP64 500 x 240 x 320: 252 / 152 / 123 us, 200 x 480 x
+// 640 (2,400 wavefronts at 2): 136 / 114 / 121 us.
+int filling_vector(int64_t px, int P, int acc) {
+  constexpr int64_t kSimds = 1024;
+  const int64_t need = (acc == DSGM_ACC_F32 || acc == DSGM_ACC_U8 ? 3 : 2) * kSimds;
+  while (P > 1 && px / (64 * P) < need) P /= 2;
+  return P;
+}
+
 // widest per-lane pixel count (up to `cap`) allowed by the sizes, strides and
 // alignments
 int pick_vector(const dsgm_shape& s, const void* const* ptrs, const size_t* elem, int n,
@@ -382,6 +399,7 @@ int forward_impl(const void* frames, dsgm_in_dtype in_dtype, dsgm_shape shape, d
   int P = std::min(widest, preferred_vector(in_dtype, acc));
   if (!legal(P)) P = 1;
   if (as_run) P = widest;  // four one-byte pixels per lane when the layout allows
+  P = filling_vector(px, P, acc);
   // 192-thread workgroups for the time-fused FP64 forward at two pixels per
   // lane: 0.8-1.3 % faster than 256 on 1920 x 2560 x 500 on two machines
   // (interleaved runs; 64 and 128 were not faster); 256 elsewhere
