@@ -87,8 +87,8 @@ __device__ __forceinline__ void fill_table(TableEntry<Acc>* tbl, int weight_rule
 
 // Compile-time variants of the forward kernels.  F_COUNT (batched kernel
 // only) adds the per-frame foreground counts of instances that have counters.
-// F_STEP (one-frame launches without checkpoints or codes) requests the
-// state before the workgroup builds its table.
+// F_STEP (one-frame launches without checkpoints or codes) requests the state
+// and the frame before the workgroup builds its table, and has no frame loop.
 enum : int { F_BG = FWD_BG, F_CODES = FWD_CODES, F_CKPT = FWD_CKPT, F_PRINTED = FWD_PRINTED,
              F_COUNT = 16, F_STEP = 32 };
 
@@ -129,7 +129,8 @@ __device__ __forceinline__ void store_state(char* const planes[6], int64_t soff,
   *reinterpret_cast<Vec<uint8_t, P>*>(planes[5] + soff) = aC;
 }
 
-// the group's six state values
+// the group's six state values, the ages as they are stored (a conversion here
+// would wait for the loads)
 template <typename Acc, int P>
 __device__ __forceinline__ void load_state(const GroupJob& j, Model<Acc>* s) {
   const int64_t o = j.soff * int64_t(sizeof(Acc));
@@ -145,17 +146,19 @@ __device__ __forceinline__ void load_state(const GroupJob& j, Model<Acc>* s) {
     s[q].vA = vA.v[q];
     s[q].mC = mC.v[q];
     s[q].vC = vC.v[q];
-    s[q].aA = age_in<Acc>(aA.v[q]);
-    s[q].aC = age_in<Acc>(aC.v[q]);
+    s[q].aA = aA.v[q];
+    s[q].aC = aC.v[q];
   }
 }
 
-// The group through its T frames; with F_STEP from the state `pre` the
-// caller has already loaded, else from the state planes.
+// The group through its T frames; with F_STEP through the one frame `x0` from
+// the state `pre`, both of which the caller has already requested, else from
+// the frames and the state planes.
 template <typename In, typename Acc, typename Io, int P, int U, int FLAGS>
 __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Acc>& k,
                                           const TableEntry<Acc>* __restrict__ tbl,
-                                          const Model<Acc>* pre = nullptr) {
+                                          const Model<Acc>* pre = nullptr,
+                                          const Vec<In, P>* x0 = nullptr) {
   constexpr bool BG = (FLAGS & F_BG) != 0;
   constexpr bool CODES = (FLAGS & F_CODES) != 0;
   constexpr bool CKPT = (FLAGS & F_CKPT) != 0;
@@ -164,7 +167,14 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
   Model<Acc> s[P];
   if constexpr ((FLAGS & F_STEP) != 0) {
 #pragma unroll
-    for (int q = 0; q < P; ++q) s[q] = pre[q];
+    for (int q = 0; q < P; ++q) {
+      s[q] = pre[q];
+      // (volatile: the conversions stay after the table's barrier, where the
+      // ages have arrived)
+      asm volatile("" : "+v"(s[q].aA), "+v"(s[q].aC));
+      s[q].aA = age_in<Acc>(s[q].aA);
+      s[q].aC = age_in<Acc>(s[q].aC);
+    }
   } else {
     // load_state's loads written out rather than called: a call compiles
     // the time-fused kernels to a different instruction schedule than the
@@ -250,6 +260,12 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
     if (CODES) *reinterpret_cast<Vec<uint8_t, P>*>(j.codes + o + j.foff) = cd;
   };
 
+  if constexpr ((FLAGS & F_STEP) != 0) {
+    do_frame(*x0, 0);
+    store_state<Acc, P>(j.state, j.soff, s);
+    return;
+  }
+
   // Full batches of U frames, software-pipelined over two register buffers:
   // the loads of batch b+1 are issued before the steps of batch b, so U frames
   // are always in flight while the lane computes.  All conditions are uniform.
@@ -309,18 +325,22 @@ template <typename In, typename Acc, typename Io, int P, int U, int FLAGS>
 __global__ void __launch_bounds__(256) fwd_kernel(const FwdArgs a) {
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
   if constexpr ((FLAGS & F_STEP) != 0) {
-    // one frame: the state is requested before the table is built, so that
-    // its latency overlaps the table's divisions and barrier
+    // one frame: the state and the frame are requested before the table is
+    // built, so that their latency overlaps the table's divisions and barrier
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const bool active = g < a.ngroups;
     const GroupJob j = step_job(a, geom::group_of(g, a.groups_per_row, P, a.W, a.row_stride));
     Model<Acc> s[P];
-    if (active) load_state<Acc, P>(j, s);
+    Vec<In, P> x0;
+    if (active) {
+      load_state<Acc, P>(j, s);
+      x0 = ld_stream<In, P>(reinterpret_cast<const In*>(j.frames) + j.foff);
+    }
     fill_table<Acc>(tbl, a.weight_rule, a.age_max, a.var_init);
     if (!active) return;  // no barrier follows
     const StepConsts<Acc> k = make_consts<Acc>(a.theta_s, a.theta_d, a.var_init, a.var_floor,
                                                a.mask_floor);
-    run_group<In, Acc, Io, P, U, FLAGS>(j, k, tbl, s);
+    run_group<In, Acc, Io, P, U, FLAGS>(j, k, tbl, s, &x0);
     return;
   }
   fill_table<Acc>(tbl, a.weight_rule, a.age_max, a.var_init);
