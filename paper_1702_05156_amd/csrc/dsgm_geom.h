@@ -116,8 +116,19 @@ constexpr int PX = 4;    // pixels per lane (one row)
 constexpr int NT = 256;  // lanes per workgroup
 static_assert(TH * TW == NT * PX, "tile = lanes x pixels");
 
-template <int RG, bool MED>
+// A tile's rows, columns and pixels per lane.  Small frames take Small: more
+// workgroups, and a quarter of the work in each lane's chain per frame.
+struct Big {
+  static constexpr int th = TH, tw = TW, px = PX;
+};
+struct Small {
+  static constexpr int th = 8, tw = 32, px = 1;
+};
+static_assert(Small::th * Small::tw == NT * Small::px, "tile = lanes x pixels");
+
+template <int RG, bool MED, typename Tile = Big>
 struct Geo {
+  static constexpr int TH = Tile::th, TW = Tile::tw, PX = Tile::px;
   static constexpr int RM = MED ? 1 : 0;       // median radius
   static constexpr int R = RG + RM;            // halo of the raw tile
   static constexpr int RAW_H = TH + 2 * R, RAW_W = TW + 2 * R;
@@ -127,8 +138,14 @@ struct Geo {
   static constexpr int HB_N = RAW_H * HB_W;
   static constexpr int GB_N = GB_H * GB_W;
   static constexpr int LOADS = (RAW_N + NT - 1) / NT;  // raw elements per lane
-  static constexpr int ROW_IT = (HB_N / 2 + NT - 1) / NT;  // row-pass output pairs per lane
-  static constexpr int COL_IT = (GB_N / 2 + NT - 1) / NT;  // column-pass output pairs per lane
+  // row pass: a lane makes ROW_SEG adjacent output pairs of one row per round
+  static constexpr int ROW_SEG = PX == 1 ? 1 : (MED ? 3 : 4);
+  static_assert((HB_W / 2) % ROW_SEG == 0, "a lane's pairs stay in one row");
+  static constexpr int ROW_ROUNDS = (HB_N / 2 + NT * ROW_SEG - 1) / (NT * ROW_SEG);
+  static constexpr int ROW_IT = ROW_SEG * ROW_ROUNDS;  // row-pass output pairs per lane
+  // column pass: a lane makes COL_IT vertically adjacent output pairs
+  static constexpr int COL_IT = PX == 1 ? 1 : (MED ? 3 : 2);
+  static_assert(GB_H % COL_IT == 0 && GB_W / 2 * (GB_H / COL_IT) <= NT, "one round");
   static constexpr int GB_IT = (GB_N + NT - 1) / NT;  // 2-D blur cells per lane (8-bit form)
 
   // the raw cell a lane stages in its l-th load, and whether it has one
@@ -143,20 +160,22 @@ struct Geo {
   }
   // the it-th output pair of the row pass: HB cells 2*pair, 2*pair + 1 from
   // the raw window starting at row_window (2*RG + 2 cells)
-  DSGM_HD static int row_pair(int tid, int it) { return tid + it * NT; }
-  DSGM_HD static bool row_active(int tid, int it) {
-    return it + 1 < ROW_IT || row_pair(tid, it) < HB_N / 2;
+  DSGM_HD static int row_pair(int tid, int it) {
+    return (tid + it / ROW_SEG * NT) * ROW_SEG + it % ROW_SEG;
   }
+  DSGM_HD static bool row_active(int tid, int it) { return row_pair(tid, it) < HB_N / 2; }
   DSGM_HD static int row_window(int pair) {
     const int r = pair / (HB_W / 2), v = 2 * (pair - r * (HB_W / 2));
     return r * RAW_W + v;
   }
   // the it-th output pair of the column pass: GB cells 2*pair, 2*pair + 1 from
-  // HB cells 2*pair + j*HB_W (+1), j < 2*RG + 1 (the two arrays share a width)
-  DSGM_HD static int col_pair(int tid, int it) { return tid + it * NT; }
-  DSGM_HD static bool col_active(int tid, int it) {
-    return it + 1 < COL_IT || col_pair(tid, it) < GB_N / 2;
+  // HB cells 2*pair + j*HB_W (+1), j < 2*RG + 1 (the two arrays share a width);
+  // pair it + 1 lies one row below pair it
+  DSGM_HD static int col_pair(int tid, int it) {
+    constexpr int CP = GB_W / 2;
+    return (tid / CP * COL_IT + it) * CP + tid % CP;
   }
+  DSGM_HD static bool col_active(int tid, int it) { return col_pair(tid, it) < GB_N / 2; }
   // the it-th cell of the two-dimensional blur (the 8-bit form): GB cell
   // `cell` from the (2*RG + 1) x (2*RG + 1) raw window whose top-left cell is
   // blur_window(cell) (GB cell (r, c) is frame pixel (y0 - RM + r, x0 - RM + c),

@@ -10,8 +10,8 @@
 // to memory unless the caller asks for it.
 //
 // Decomposition: a workgroup of 256 lanes owns a TH x TW = 16 x 64 tile of
-// pixels for all T frames, each lane four horizontally adjacent pixels of one
-// row, with their model state in registers.  Per frame the workgroup stages
+// pixels (8 x 32 for small frames) for all T frames, each lane four (one)
+// horizontally adjacent pixels of one row, with their model state in registers.  Per frame the workgroup stages
 // the tile plus a halo of R = RG (+1 with the median) rows and columns of the
 // raw frame in LDS (indices clamped to the frame), runs the row pass and the
 // column pass of the blur in LDS, then each lane takes the median of its
@@ -21,14 +21,21 @@
 // contiguous range of them: neighbouring tiles, whose halos overlap, run on
 // the same L2.
 //
+// The kernel is bound by vector issue, then by LDS: a lane's blur outputs are
+// adjacent (six in one row, two columns of three rows), so that it reads every
+// value of its windows once; the medians are plain min/max instructions.  With
+// these and the update under lane masks 1080 x 1920 frames, 5 taps and median,
+// went from 516 to 447 us (FP64, 50 frames) and 285 to 237 us (BF16/FP32).
+//
 // Median of nine: sort each of the three columns of the neighbourhood; the
 // median is then the median of (largest column minimum, median of the column
 // medians, smallest column maximum).  Four adjacent pixels share their column
-// sorts (six columns), so a pixel costs about 21 min/max.  All selections
-// are exact.
+// sorts (six columns).  All selections are exact.
 //
 // The blur sums run from 0 in index order with every product and sum rounded
 // (no contraction) for FP64 state, the order the oracle uses.
+#include <type_traits>
+
 #include "dsgm_ext.h"
 #include "dsgm_fwd_impl.h"
 
@@ -39,25 +46,81 @@ namespace pre {
 using fwd::fill_table;
 using fwd::make_consts;
 
-// tile shape and every tile cell index: dsgm_geom.h
-using geom::pre::TH;
-using geom::pre::TW;
-using geom::pre::PX;
+// tile shapes and every tile cell index: dsgm_geom.h
 using geom::pre::NT;
-template <int RG, bool MED>
-using Geo = geom::pre::Geo<RG, MED>;
+using geom::pre::Geo;
 
-// min and max of finite values (v_min/v_max; a zero's sign may differ from a
-// sort's when +0 and -0 tie, which leaves every value unchanged)
-__device__ __forceinline__ double mn(double a, double b) { return __builtin_fmin(a, b); }
-__device__ __forceinline__ double mx(double a, double b) { return __builtin_fmax(a, b); }
-__device__ __forceinline__ float mn(float a, float b) { return __builtin_fminf(a, b); }
-__device__ __forceinline__ float mx(float a, float b) { return __builtin_fmaxf(a, b); }
+// min and max of finite values (a zero's sign may differ from a sort's when +0
+// and -0 tie, which leaves every value unchanged).  The instructions themselves:
+// the builtins add a canonicalising max per value read from LDS, 9 of 30
+// instructions per pixel with FP64 state.
+__device__ __forceinline__ double mn(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double mx(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 
-// median of three
-template <typename Acc>
-__device__ __forceinline__ Acc med3(Acc a, Acc b, Acc c) {
-  return mx(mn(a, b), mn(mx(a, b), c));
+// The medians of PX horizontally adjacent pixels from the three rows of their
+// PX + 2 columns: each column sorted once, then per pixel the median of (the
+// largest column minimum, the median of the column medians, the smallest
+// column maximum).  FP64: two pixels share the pairs of the columns they have
+// in common.  FP32: the three-operand instructions, 8.5 per pixel.
+template <int PX>
+__device__ __forceinline__ void medians(const double (&p)[3][PX + 2], double (&xs)[PX]) {
+  double lo[PX + 2], md[PX + 2], hi[PX + 2];
+#pragma unroll
+  for (int d = 0; d < PX + 2; ++d) {
+    const double l01 = mn(p[0][d], p[1][d]), h01 = mx(p[0][d], p[1][d]);
+    lo[d] = mn(l01, p[2][d]);
+    const double h = mx(l01, p[2][d]);
+    hi[d] = mx(h01, h);
+    md[d] = mn(h01, h);
+  }
+#pragma unroll
+  for (int q0 = 0; q0 < PX; q0 += 2) {  // pixels q0, q0 + 1 have columns q0 + 1, q0 + 2 in common
+    const double l = mx(lo[q0 + 1], lo[q0 + 2]), h = mn(hi[q0 + 1], hi[q0 + 2]);
+    const double ml = mn(md[q0 + 1], md[q0 + 2]), mh = mx(md[q0 + 1], md[q0 + 2]);
+#pragma unroll
+    for (int q = q0; q < q0 + 2 && q < PX; ++q) {
+      const int o = q == q0 ? q0 : q0 + 3;  // the pixel's other column
+      const double a = mx(l, lo[o]), c = mn(h, hi[o]), b = mx(ml, mn(mh, md[o]));
+      xs[q] = mx(mn(a, b), mn(mx(a, b), c));
+    }
+  }
+}
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float med3(float a, float b, float c) {
+  float r;
+  asm("v_med3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+template <int PX>
+__device__ __forceinline__ void medians(const float (&p)[3][PX + 2], float (&xs)[PX]) {
+  float lo[PX + 2], md[PX + 2], hi[PX + 2];
+#pragma unroll
+  for (int d = 0; d < PX + 2; ++d) {
+    lo[d] = min3(p[0][d], p[1][d], p[2][d]);
+    md[d] = med3(p[0][d], p[1][d], p[2][d]);
+    hi[d] = max3(p[0][d], p[1][d], p[2][d]);
+  }
+#pragma unroll
+  for (int q = 0; q < PX; ++q)
+    xs[q] = med3(max3(lo[q], lo[q + 1], lo[q + 2]), med3(md[q], md[q + 1], md[q + 2]),
+                 min3(hi[q], hi[q + 1], hi[q + 2]));
 }
 
 // blur sum over n taps from 0 in index order (no contraction for double)
@@ -68,16 +131,26 @@ __device__ __forceinline__ float tap<float>(float acc, float w, float x) {
   return __builtin_fmaf(w, x, acc);
 }
 
-template <typename In, typename Acc, typename Io, int RG, bool MED, bool PRINTED>
+// Frames of fewer 16 x 64 tiles than this (two per CU) are cut into 8 x 32 tiles
+// of one pixel per lane: with few workgroups the chain of a tile's frames bounds
+// the call, and a quarter of the pixels per lane shortens it.  16 x 64 against
+// 8 x 32 tiles, 5 taps and median: FP64 500 x 240 x 320 (75 tiles) 791 / 527 us,
+// 100 x 480 x 640 (300) 226 / 176 us, 50 x 720 x 1280 (900) 228 / 233 us,
+// 50 x 1080 x 1920 (2,040) 450 / 525 us; BF16/FP32 601 / 379, 151 / 113,
+// 124 / 142 and 238 / 297 us.
+constexpr int64_t SMALL_BELOW = 512;
+
+template <typename In, typename Acc, typename Io, int RG, bool MED, bool PRINTED, typename Tile>
 __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
-  using G = Geo<RG, MED>;
+  using G = Geo<RG, MED, Tile>;
+  constexpr int TH = G::TH, TW = G::TW, PX = G::PX;
   // raw, row-blurred and blurred tiles each have their own storage, so a frame
   // needs three barriers: the next frame's raw tile can be staged while slow
   // lanes still read this frame's blurred tile (without a blur the raw tile is
   // the blurred tile and a fourth barrier guards it)
-  __shared__ Acc buf_raw[G::RAW_N];
-  __shared__ Acc buf_hb[RG > 0 ? G::HB_N : 1];
-  __shared__ Acc buf_gb[RG > 0 ? G::GB_N : 1];
+  __shared__ alignas(16) Acc buf_raw[G::RAW_N];
+  __shared__ alignas(16) Acc buf_hb[RG > 0 ? G::HB_N : 1];
+  __shared__ alignas(16) Acc buf_gb[RG > 0 ? G::GB_N : 1];
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
   fill_table<Acc>(tbl, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
   const StepConsts<Acc> k =
@@ -107,6 +180,8 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
   for (int d = 0; d < 3; ++d) gr[d] = G::med_row(gy, d, y0, a.H);
 #pragma unroll
   for (int d = 0; d < PX + 2; ++d) gc[d] = G::med_col(x0 + tx, d, x0, a.W);
+  // a tile inside the frame clamps nothing: its medians' columns are adjacent
+  const bool inside = y0 > 0 && y0 + TH < a.H && x0 > 0 && x0 + TW < a.W;
 
   bool valid[PX];
   bool all_valid = gy < a.H;
@@ -136,13 +211,13 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
     }
   }
 
-  // this lane's outputs of the row and column passes (pairs of adjacent
-  // outputs, lane-strided) and the row pass's window start in the raw tile:
-  // the same every frame
-  constexpr int ROW_IT = G::ROW_IT, COL_IT = G::COL_IT;
-  uint32_t row_src[ROW_IT];
+  // the start of this lane's raw window in each round of the row pass, and its
+  // first cell of the column pass: the same every frame
+  uint32_t row_src[G::ROW_ROUNDS];
 #pragma unroll
-  for (int it = 0; it < ROW_IT; ++it) row_src[it] = uint32_t(G::row_window(G::row_pair(tid, it)));
+  for (int rd = 0; rd < G::ROW_ROUNDS; ++rd)
+    row_src[rd] = uint32_t(G::row_window(G::row_pair(tid, rd * G::ROW_SEG)));
+  const int col_src = 2 * G::col_pair(tid, 0);
 
   const In* frames = static_cast<const In*>(a.frames);
   In nxt[G::LOADS];
@@ -165,45 +240,49 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
     const Acc* gbp;  // the blurred tile, GB_H x GB_W
     if constexpr (RG > 0) {
       // 2. row pass: hb[r][v] = sum_j w_j raw[r][v + j], v in [0, HB_W).  A
-      // lane makes two horizontally adjacent outputs per step from one window
-      // of 2*RG + 2 values (HB_W is even, so a pair never straddles rows)
+      // lane makes ROW_SEG adjacent output pairs of one row from one window
       static_assert(G::HB_W % 2 == 0 && G::GB_W % 2 == 0, "output pairs stay in one row");
+      constexpr int NO = 2 * G::ROW_SEG;
 #pragma unroll
-      for (int it = 0; it < ROW_IT; ++it) {
-        const int pi = G::row_pair(tid, it);
-        if (G::row_active(tid, it)) {
-          const Acc* src = buf_raw + row_src[it];
-          Acc win[2 * RG + 2];
+      for (int rd = 0; rd < G::ROW_ROUNDS; ++rd) {
+        if (G::row_active(tid, rd * G::ROW_SEG)) {
+          const Acc* src = buf_raw + row_src[rd];
+          Acc* dst = buf_hb + 2 * G::row_pair(tid, rd * G::ROW_SEG);
+          Acc win[NO + 2 * RG];
 #pragma unroll
-          for (int j = 0; j < 2 * RG + 2; ++j) win[j] = src[j];
-          Acc a0 = Acc(0), a1 = Acc(0);
+          for (int j = 0; j < NO + 2 * RG; ++j) win[j] = src[j];
 #pragma unroll
-          for (int j = 0; j < 2 * RG + 1; ++j) {
-            a0 = tap(a0, wt[j], win[j]);
-            a1 = tap(a1, wt[j], win[j + 1]);
+          for (int o = 0; o < NO; ++o) {
+            Acc sum = Acc(0);
+#pragma unroll
+            for (int j = 0; j < 2 * RG + 1; ++j) sum = tap(sum, wt[j], win[o + j]);
+            dst[o] = sum;
           }
-          buf_hb[2 * pi] = a0;
-          buf_hb[2 * pi + 1] = a1;
         }
       }
       __syncthreads();
       // 3. column pass: gb[r][v] = sum_i w_i hb[r + i][v], r in [0, GB_H); the
-      // two tiles have the same width, so gb's row-major index is hb's
+      // two tiles have the same width, so gb's row-major index is hb's.  A lane
+      // makes COL_IT output pairs of one column pair, reading each row once
       static_assert(G::HB_W == G::GB_W, "row-blurred and blurred tiles share a width");
+      if (G::col_active(tid, 0)) {
+        const Acc* src = buf_hb + col_src;
+        Acc* dst = buf_gb + col_src;
+        Acc in[G::COL_IT + 2 * RG][2];
 #pragma unroll
-      for (int it = 0; it < COL_IT; ++it) {
-        const int pi = G::col_pair(tid, it);
-        if (G::col_active(tid, it)) {
-          const Acc* src = buf_hb + 2 * pi;
-          Acc a0 = Acc(0), a1 = Acc(0);
-#pragma unroll
-          for (int j = 0; j < 2 * RG + 1; ++j) {
-            a0 = tap(a0, wt[j], src[j * G::HB_W]);
-            a1 = tap(a1, wt[j], src[j * G::HB_W + 1]);
-          }
-          buf_gb[2 * pi] = a0;
-          buf_gb[2 * pi + 1] = a1;
+        for (int j = 0; j < G::COL_IT + 2 * RG; ++j) {
+          in[j][0] = src[j * G::HB_W];
+          in[j][1] = src[j * G::HB_W + 1];
         }
+#pragma unroll
+        for (int o = 0; o < G::COL_IT; ++o)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            Acc sum = Acc(0);
+#pragma unroll
+            for (int j = 0; j < 2 * RG + 1; ++j) sum = tap(sum, wt[j], in[o + j][c]);
+            dst[o * G::GB_W + c] = sum;
+          }
       }
       __syncthreads();
       gbp = buf_gb;
@@ -214,25 +293,20 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
     // 4. median of each pixel's 3 x 3 neighbourhood, then the model update
     Acc xs[PX];
     if constexpr (MED) {
-      Acc lo[PX + 2], md[PX + 2], hi[PX + 2];
+      Acc p[3][PX + 2];
+      if (inside) {
+        const Acc* nb = gbp + ty * G::GB_W + tx;
 #pragma unroll
-      for (int d = 0; d < PX + 2; ++d) {
-        const Acc p0 = gbp[gr[0] * G::GB_W + gc[d]];
-        const Acc p1 = gbp[gr[1] * G::GB_W + gc[d]];
-        const Acc p2 = gbp[gr[2] * G::GB_W + gc[d]];
-        const Acc l01 = mn(p0, p1), h01 = mx(p0, p1);
-        lo[d] = mn(l01, p2);
-        const Acc h = mx(l01, p2);
-        hi[d] = mx(h01, h);
-        md[d] = mn(h01, h);
-      }
+        for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int q = 0; q < PX; ++q) {
-        const Acc a0 = mx(mx(lo[q], lo[q + 1]), lo[q + 2]);
-        const Acc b0 = med3(md[q], md[q + 1], md[q + 2]);
-        const Acc c0 = mn(mn(hi[q], hi[q + 1]), hi[q + 2]);
-        xs[q] = med3(a0, b0, c0);
+          for (int d = 0; d < PX + 2; ++d) p[r][d] = nb[r * G::GB_W + d];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+          for (int d = 0; d < PX + 2; ++d) p[r][d] = gbp[gr[r] * G::GB_W + gc[d]];
       }
+      medians<PX>(p, xs);
     } else {
 #pragma unroll
       for (int q = 0; q < PX; ++q) xs[q] = gbp[gr[1] * G::GB_W + gc[q + 1]];
@@ -249,33 +323,36 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
 #pragma unroll
       for (int q = 0; q < PX; ++q) exchange<Acc>(s[q], xs[q], k, rec[q]);
     }
-    Vec<uint8_t, PX> mk, cd;
-    Vec<Io, PX> bgv;
-    Vec<Io, PX> fv;  // the filtered frame in the array type
+    uint64_t back[PX];  // lanes whose pixel q is background
 #pragma unroll
     for (int q = 0; q < PX; ++q) {
-      rec[q].fg = fg_from<Acc, PRINTED>(rec[q].qd, s[q], xs[q], k);
-      mk.v[q] = rec[q].fg ? uint8_t(255) : uint8_t(0);
-      cd.v[q] = uint8_t(code_of<Acc>(rec[q]));
-      bgv.v[q] = Io(s[q].mA);
-      fv.v[q] = Io(xs[q]);
+      const bool b = bg_from<Acc, PRINTED>(rec[q].qd, s[q], xs[q], k);
+      back[q] = __builtin_amdgcn_ballot_w64(b);
+      rec[q].fg = !b;
     }
+    using Mask = Vec<uint8_t, PX>;
+    const auto mk = __builtin_bit_cast(
+        Mask, typename fwd::Raw<PX>::type(mask_bytes<PX>(back)));
+    // one output array's PX values of this frame (the optional outputs are
+    // formed under their uniform branches)
     const int64_t o = t * a.frame_stride + foff;
-    if (vec_ok) {
-      *reinterpret_cast<Vec<uint8_t, PX>*>(a.masks + o) = mk;
-      if (a.bg) *reinterpret_cast<Vec<Io, PX>*>(static_cast<Io*>(a.bg) + o) = bgv;
-      if (a.filtered) *reinterpret_cast<Vec<Io, PX>*>(static_cast<Io*>(a.filtered) + o) = fv;
-      if (a.codes) *reinterpret_cast<Vec<uint8_t, PX>*>(a.codes + o) = cd;
-    } else {
+    auto put = [&](auto* out, auto value) {
+      using X = std::remove_pointer_t<decltype(out)>;
+      if (vec_ok) {
+        Vec<X, PX> v;
 #pragma unroll
-      for (int q = 0; q < PX; ++q) {
-        if (!valid[q]) continue;
-        a.masks[o + q] = mk.v[q];
-        if (a.bg) static_cast<Io*>(a.bg)[o + q] = bgv.v[q];
-        if (a.filtered) static_cast<Io*>(a.filtered)[o + q] = fv.v[q];
-        if (a.codes) a.codes[o + q] = cd.v[q];
+        for (int q = 0; q < PX; ++q) v.v[q] = value(q);
+        *reinterpret_cast<Vec<X, PX>*>(out + o) = v;
+      } else {
+#pragma unroll
+        for (int q = 0; q < PX; ++q)
+          if (valid[q]) out[o + q] = value(q);
       }
-    }
+    };
+    put(a.masks, [&](int q) { return mk.v[q]; });
+    if (a.bg) put(static_cast<Io*>(a.bg), [&](int q) { return Io(s[q].mA); });
+    if (a.filtered) put(static_cast<Io*>(a.filtered), [&](int q) { return Io(xs[q]); });
+    if (a.codes) put(a.codes, [&](int q) { return uint8_t(code_of<Acc>(rec[q])); });
     if constexpr (RG == 0) __syncthreads();  // the next frame overwrites the raw tile
   }
 
@@ -291,18 +368,28 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
   }
 }
 
-template <typename In, typename Acc, typename Io, bool MED, bool PRINTED>
-hipError_t launch_rg(const PreArgs& a, int rg, hipStream_t stream) {
-  const int64_t nb = a.tiles_x * a.tiles_y;
-  const dim3 grid{uint32_t(nb), 1, 1}, block{NT, 1, 1};
+template <typename In, typename Acc, typename Io, bool MED, bool PRINTED, typename Tile>
+hipError_t launch_tile(PreArgs a, int rg, hipStream_t stream) {
+  a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
+  a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
+  const dim3 grid{uint32_t(a.tiles_x * a.tiles_y), 1, 1}, block{NT, 1, 1};
   switch (rg) {
-    case 0: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 0, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 1: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 1, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 2, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 3: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 3, MED, PRINTED>), grid, block, 0, stream, a); break;
+    case 0: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 0, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
+    case 1: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 1, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
+    case 2: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 2, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
+    case 3: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 3, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <typename In, typename Acc, typename Io, bool MED, bool PRINTED>
+hipError_t launch_rg(const PreArgs& a, int rg, hipStream_t stream) {
+  using geom::pre::Big;
+  using geom::pre::Small;
+  if (a.tiles_x * a.tiles_y < SMALL_BELOW)  // tiles of 16 x 64 (the caller's count)
+    return launch_tile<In, Acc, Io, MED, PRINTED, Small>(a, rg, stream);
+  return launch_tile<In, Acc, Io, MED, PRINTED, Big>(a, rg, stream);
 }
 
 template <typename In, typename Acc, typename Io>

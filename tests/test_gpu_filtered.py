@@ -75,6 +75,20 @@ def test_filtered_edge_shapes(T, H, W):
         G.assert_bit_exact(k, hs[k], ref[k])
 
 
+@pytest.mark.parametrize("n,median", [(5, 1), (3, 1), (7, 1), (5, 0), (3, 0), (7, 0), (0, 1)])
+@pytest.mark.parametrize("W", [1462, 1461])
+def test_filtered_large_frame_tiles_f64_bit_exact(n, median, W):
+    """Frames of 512 tiles and more run 16 x 64 tiles (the smaller ones above
+    8 x 32): ragged in both directions, with vector and single stores."""
+    T, H = 3, 365   # 23 x 23 tiles
+    p, out, st, xf, st0 = _case(46, T, H, W, n, median)
+    G.assert_bit_exact("filtered", G.flat(out["filtered"]), xf)
+    ref = oracle.forward(xf, st0, G.oracle_params(p))
+    G.assert_bit_exact("codes", G.flat(out["codes"]), ref["codes"])
+    G.assert_bit_exact("masks", G.flat(out["masks"]), ref["masks"])
+    G.assert_bit_exact("bg", G.flat(out["bg"]), ref["bg"])
+
+
 def test_filtered_strided_frames():
     """Frames that are a view with row and frame padding (scalar stores)."""
     T, H, W = 9, 20, 70
