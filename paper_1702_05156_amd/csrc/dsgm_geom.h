@@ -124,7 +124,11 @@ struct Big {
 struct Small {
   static constexpr int th = 8, tw = 32, px = 1;
 };
-static_assert(Small::th * Small::tw == NT * Small::px, "tile = lanes x pixels");
+struct Wide {
+  static constexpr int th = 8, tw = 64, px = 2;
+};
+static_assert(Small::th * Small::tw == NT * Small::px && Wide::th * Wide::tw == NT * Wide::px,
+              "tile = lanes x pixels");
 
 template <int RG, bool MED, typename Tile = Big>
 struct Geo {
@@ -144,7 +148,7 @@ struct Geo {
   static constexpr int ROW_ROUNDS = (HB_N / 2 + NT * ROW_SEG - 1) / (NT * ROW_SEG);
   static constexpr int ROW_IT = ROW_SEG * ROW_ROUNDS;  // row-pass output pairs per lane
   // column pass: a lane makes COL_IT vertically adjacent output pairs
-  static constexpr int COL_IT = PX == 1 ? 1 : (MED ? 3 : 2);
+  static constexpr int COL_IT = PX == 1 ? 1 : (MED && PX == 4 ? 3 : 2);
   static_assert(GB_H % COL_IT == 0 && GB_W / 2 * (GB_H / COL_IT) <= NT, "one round");
   static constexpr int GB_IT = (GB_N + NT - 1) / NT;  // 2-D blur cells per lane (8-bit form)
 

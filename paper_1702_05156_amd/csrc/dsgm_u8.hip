@@ -10,6 +10,8 @@
 // integers), and per frame reads P frame bytes and writes P mask bytes.
 // The state is 6 bytes per pixel instead of 68, which is what a T = 1
 // streaming caller moves per frame; such calls run u8_step_kernel below.
+#include <cmath>
+
 #include "dsgm_ext.h"
 #include "dsgm_fwd_impl.h"
 
@@ -412,7 +414,8 @@ __global__ void __launch_bounds__(256) u8_init_kernel(const FwdArgs a) {
 // update on it.  Two barriers per frame: after the raw bytes are staged and
 // after the blurred bytes are written; the next frame's bytes are loaded into
 // registers while the current one is filtered.  All tile cell indices come
-// from geom::pre::Geo.
+// from geom::pre::Geo.  Calls with decision codes, without a blur, or with
+// weights that the fixed-point form below cannot hold run this kernel.
 template <int RG, bool MED, bool PRINTED>
 __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) {
   using G = geom::pre::Geo<RG, MED>;
@@ -555,12 +558,8 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
     }
 
     Vec<uint8_t, PX> mk, cd, fv;
-    if (a.codes)
-      mk = __builtin_bit_cast(decltype(mk),
-                              frame8<PX, true, true, PRINTED>(s, xs, var_init, tbl, cd));
-    else
-      mk = __builtin_bit_cast(decltype(mk),
-                              frame8<PX, true, false, PRINTED>(s, xs, var_init, tbl, cd));
+    mk = __builtin_bit_cast(decltype(mk),
+                            frame8<PX, true, true, PRINTED>(s, xs, var_init, tbl, cd));
 #pragma unroll
     for (int q = 0; q < PX; ++q) fv.v[q] = uint8_t(xs[q]);
     uint8_t* const filt = static_cast<uint8_t*>(a.filtered);
@@ -594,14 +593,447 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
   }
 }
 
+// ------------------------------------------------- the blur on matrix cores
+// The appendix's blurred byte is the integer part of a sum of N x N rounded
+// products, added one by one in single precision (50 vector instructions and 25
+// LDS reads a pixel for 5 taps, which bounded pre_u8_kernel).  Here the same sum
+// is first formed exactly in fixed point by the matrix cores: the weights are
+// rounded to multiples of 2^-24, split into three signed bytes, and the window
+// sums are products of 8-bit matrices with 32-bit sums.  How far the
+// single-precision result can lie from that sum is known (the weights' rounding
+// and the bound on the rounding of every product and addition, blur_fits()), so
+// its integer part is known too unless an integer lies that near the sum; those
+// cells (about one in 3,000 on noisy frames) are evaluated in single precision, in
+// the appendix's order.
+//
+// One matrix product covers 16 windows of 16 bytes in four rows: column n of B
+// is a window (lane n % 16 holds 16 bytes of row lane / 16), row m of A the
+// weights of the window's output m, a diagonal band, so that a product gives OW
+// adjacent blurred cells of each of 16 windows.  Rows beyond the fourth are a
+// second product.  Each wavefront takes every fourth group of 16 windows.
+//
+// Tiles are 8 x 64 pixels, two per lane: a wavefront has one group of windows a
+// frame (60 of the 64 windows are used with 5 taps) and four workgroups fit a
+// CU; 16 x 64 tiles, four pixels per lane, needed 192 registers (1,047 against
+// 908 us for 50 frames of 1920 x 2560).  Frames of fewer 16 x 64 tiles than
+// SMALL8_BELOW take 8 x 32 tiles, one pixel per lane (8 x 64 / 8 x 32 tiles):
+// 500 x 240 x 320 (75) 699 / 563 us, 100 x 360 x 480 (184) 160 / 129 us,
+// 100 x 480 x 640 (300) 175 / 210 us, 50 x 1080 x 1920 (2,040) 365 / 465 us.
+// Bound by vector issue (about 90 instructions a pixel, half of them the 8-bit
+// update).  pre_u8_kernel, which sums the windows in single precision, took
+// 1,182, 253, 300 and 507 us; 50 x 1920 x 2560: 1,091 against 801 us, and where
+// all windows are flat (every sum undecided, a table gives the byte) 482 against
+// 404 us for 50 x 1080 x 1920.
+constexpr int64_t SMALL8_BELOW = 256;
+
+typedef int32_t V4 __attribute__((ext_vector_type(4)));
+
+template <int RG, bool MED, typename Tile>
+struct Geo8 {
+  using G = geom::pre::Geo<RG, MED, Tile>;
+  static constexpr int N = 2 * RG + 1;
+  static constexpr int OW = RG < 3 ? 12 : 8;               // outputs of a window: OW + N - 1 <= 16
+  static constexpr int CG = (G::GB_W + OW - 1) / OW;       // windows of a row
+  static constexpr int GBP = CG * OW;                      // pitch of the blurred tile, cells
+  static constexpr int DW = (G::RAW_W + 3) / 4;            // staged dwords of a raw row
+  static constexpr int RP = (OW * (CG - 1) + 16) / 4 > DW ? (OW * (CG - 1) + 16) / 4 : DW;
+  static constexpr int CELLS = G::RAW_H * DW;              // staged dwords of a tile
+  static constexpr int LD = (CELLS + geom::pre::NT - 1) / geom::pre::NT;
+  static constexpr int WIN = G::GB_H * CG;                 // windows of a tile
+  static constexpr int GROUPS = (WIN + 15) / 16;
+  static constexpr int SETS = N > 4 ? 2 : 1;               // products per group and digit
+  static_assert(OW + N - 1 <= 16 && OW % 4 == 0, "a window's outputs read its 16 bytes");
+};
+
+__device__ __forceinline__ uint32_t min3u(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_min3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ uint32_t med3u(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ uint32_t max3u(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_max3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// the window weight float(w_i * w_j) of entry e = i*N + j, and its fixed point
+template <int N>
+__device__ __forceinline__ float window_weight(const double* w, int e) {
+  const int i = e / N, j = e - i * N;
+  double wi = w[0], wj = w[0];
+#pragma unroll
+  for (int q = 1; q < N; ++q) {
+    wi = i == q ? w[q] : wi;
+    wj = j == q ? w[q] : wj;
+  }
+  return float(wi * wj);
+}
+__device__ __forceinline__ int32_t fixed24(float w) {
+  return int32_t(__builtin_rint(double(w) * 16777216.0));
+}
+
+template <int RG, bool MED, bool PRINTED, typename Tile>
+__global__ void __launch_bounds__(geom::pre::NT)
+    __attribute__((amdgpu_waves_per_eu(4))) pre_u8_mfma_kernel(const PreArgs a) {
+  using E = Geo8<RG, MED, Tile>;
+  using G = typename E::G;
+  constexpr int N = E::N, PX = G::PX, TH = G::TH, TW = G::TW, NT = geom::pre::NT;
+  __shared__ alignas(16) uint32_t raw[G::RAW_H * E::RP];   // bytes with the top bit flipped
+  __shared__ alignas(16) uint32_t gb[G::GB_H * E::GBP];    // blurred bytes, one to a dword
+  __shared__ Tables8 tbl;
+  __shared__ float wf[N * N];
+  __shared__ uint32_t flat[256];  // the blurred byte of a window of one level
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const StepConsts<double> k =
+      make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
+  for (int e = tid; e < N * N; e += NT) wf[e] = window_weight<N>(a.w, e);
+  fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
+  const uint32_t var_init = uint32_t(a.var_init);
+
+  // A: output m = lane % 16, row group lane / 16, byte j: the weight's digit of
+  // window row dy, window column j - m
+  const int m = lane & 15, rgrp = lane >> 4;
+  V4 A[E::SETS][3];
+#pragma unroll
+  for (int st = 0; st < E::SETS; ++st)
+#pragma unroll
+    for (int dw = 0; dw < 4; ++dw) {
+      uint32_t dig[3] = {0u, 0u, 0u};
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int j = 4 * dw + b, dy = 4 * st + rgrp;
+        const bool in = dy < N && j >= m && j - m < N && m < E::OW;
+        const int32_t W = in ? fixed24(wf[dy * N + j - m]) : 0;
+        const int32_t d0 = int8_t(W), W1 = (W - d0) >> 8, d1 = int8_t(W1), d2 = (W1 - d1) >> 8;
+        dig[0] |= uint32_t(d0 & 0xFF) << (8 * b);
+        dig[1] |= uint32_t(d1 & 0xFF) << (8 * b);
+        dig[2] |= uint32_t(d2 & 0xFF) << (8 * b);
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) A[st][q][dw] = int32_t(dig[q]);
+    }
+  // the bytes are staged less 128: the sum gets 128 times the weights back
+  // and the sum's upper end is what is formed: its integer part is the result's
+  // unless the integer lies less than blur_width below it
+  int32_t centre = int32_t(a.blur_above);
+  for (int e = 0; e < N * N; ++e) centre += 128 * fixed24(wf[e]);
+  const uint32_t width8 = a.blur_width << 8;  // compared with the fraction in the top 24 bits
+  float w2[N * N];  // the window's weights in scalar registers
+#pragma unroll
+  for (int e = 0; e < N * N; ++e)
+    w2[e] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wf[e])));
+  for (int c = tid; c < 256; c += NT) {  // (read after the frame loop's first barrier)
+    float blur = 0.0f;
+    for (int e = 0; e < N * N; ++e) {
+      const float prod = float(c) * wf[e];
+      blur = blur + prod;
+    }
+    flat[c] = uint32_t(__builtin_fminf(255.0f, blur));
+  }
+
+  const int64_t tile = tile_of(blockIdx.x, gridDim.x);
+  const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
+  const int ty = G::lane_row(tid), tx = G::lane_col(tid);
+  const int64_t gy = y0 + ty;
+
+  // this lane's staged dwords: frame row offset, first column, LDS index.  Where
+  // no column of the tile leaves the frame a dword is one (unaligned) load.
+  const bool inner = x0 >= G::R && x0 - G::R + 4 * E::DW <= a.W;
+  uint32_t roff[E::LD], slot[E::LD];
+  int32_t xb[E::LD];
+#pragma unroll
+  for (int l = 0; l < E::LD; ++l) {
+    const int i = tid + l * NT < E::CELLS ? tid + l * NT : 0;
+    const int r = i / E::DW, c = i - r * E::DW;
+    roff[l] = uint32_t(geom::clamp64(y0 - G::R + r, a.H - 1) * a.row_stride);  // < 2^31 (host check)
+    xb[l] = int32_t(x0) - G::R + 4 * c;
+    slot[l] = uint32_t(r * E::RP + c);
+  }
+  // the median's rows and columns in the blurred tile, clamped to the frame
+  int gr[3], gc[PX + 2];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) gr[d] = G::med_row(gy, d, y0, a.H);
+#pragma unroll
+  for (int d = 0; d < PX + 2; ++d) gc[d] = G::med_col(x0 + tx, d, x0, a.W);
+  const bool inside = y0 > 0 && y0 + TH < a.H && x0 > 0 && x0 + TW < a.W;
+
+  bool valid[PX];
+  bool all_valid = gy < a.H;
+#pragma unroll
+  for (int q = 0; q < PX; ++q) {
+    valid[q] = gy < a.H && x0 + tx + q < a.W;
+    all_valid = all_valid && valid[q];
+  }
+  const int64_t pix = gy * a.W + x0 + tx;
+  const int64_t foff = gy * a.row_stride + x0 + tx;
+  const bool vec_ok = all_valid && (a.row_stride % PX) == 0 && (a.frame_stride % PX) == 0 &&
+                      (a.W % PX) == 0;
+
+  uint8_t* const planes[4] = {static_cast<uint8_t*>(a.mean_a), static_cast<uint8_t*>(a.var_a),
+                              static_cast<uint8_t*>(a.mean_c), static_cast<uint8_t*>(a.var_c)};
+  Model8 s[PX];
+  {
+    Planes8<PX> b;
+#pragma unroll
+    for (int q = 0; q < PX; ++q) {
+      b.mA.v[q] = valid[q] ? planes[0][pix + q] : uint8_t(0);
+      b.vA.v[q] = valid[q] ? planes[1][pix + q] : uint8_t(0);
+      b.mC.v[q] = valid[q] ? planes[2][pix + q] : uint8_t(0);
+      b.vC.v[q] = valid[q] ? planes[3][pix + q] : uint8_t(0);
+      b.aA.v[q] = valid[q] ? a.age_a[pix + q] : uint8_t(1);
+      b.aC.v[q] = valid[q] ? a.age_c[pix + q] : uint8_t(1);
+    }
+    unpack8<PX>(b, tbl, s);
+  }
+
+  const uint8_t* frames = static_cast<const uint8_t*>(a.frames);
+  uint32_t nxt[E::LD];
+  auto load_frame = [&](int64_t t) {
+    const uint8_t* f = frames + t * a.frame_stride;
+    typedef uint32_t U1 __attribute__((aligned(1)));
+    if (inner) {
+#pragma unroll
+      for (int l = 0; l < E::LD; ++l)
+        nxt[l] = *reinterpret_cast<const U1*>(f + roff[l] + uint32_t(xb[l]));
+    } else {
+#pragma unroll
+      for (int l = 0; l < E::LD; ++l) {
+        nxt[l] = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int64_t xx = geom::clamp64(xb[l] + b, a.W - 1);
+          nxt[l] |= uint32_t(f[roff[l] + xx]) << (8 * b);
+        }
+      }
+    }
+  };
+  if (a.T > 0) load_frame(0);
+
+  for (int64_t t = 0; t < a.T; ++t) {
+    // 1. stage the raw bytes, then start loading the next frame's
+#pragma unroll
+    for (int l = 0; l < E::LD; ++l)
+      if (l + 1 < E::LD || tid + l * NT < E::CELLS) raw[slot[l]] = nxt[l] ^ 0x80808080u;
+    __syncthreads();
+    if (t + 1 < a.T) load_frame(t + 1);
+
+    // 2. the blurred bytes of the tile and the median's halo
+    for (int grp = wave; grp < E::GROUPS; grp += NT / 64) {
+      const int win = grp * 16 + m, wr = win < E::WIN ? win / E::CG : 0;
+      const int wc = win < E::WIN ? (win - wr * E::CG) * E::OW : 0;
+      V4 acc[3] = {V4{centre, centre, centre, centre}, V4{0, 0, 0, 0}, V4{0, 0, 0, 0}};
+#pragma unroll
+      for (int st = 0; st < E::SETS; ++st) {
+        // rows past the window carry zero weights; they read its last row
+        const int dy = 4 * st + rgrp < N ? 4 * st + rgrp : N - 1;
+        const uint32_t* src = raw + (wr + dy) * E::RP + wc / 4;
+        const V4 B = {int32_t(src[0]), int32_t(src[1]), int32_t(src[2]), int32_t(src[3])};
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          acc[q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[st][q], B, acc[q], 0, 0, 0);
+      }
+      // this lane has outputs 4*rgrp .. + 3 of its window
+      uint32_t out[4], frac[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t sum =
+            (((uint32_t(acc[2][i]) << 8) + uint32_t(acc[1][i])) << 8) + uint32_t(acc[0][i]);
+        out[i] = sum >> 24;
+        frac[i] = sum << 8;
+      }
+      const bool mine = win < E::WIN && 4 * rgrp < E::OW && wc + 4 * rgrp < G::GB_W;
+      const uint32_t low = frac[0] < frac[1] ? frac[0] : frac[1];
+      if (__builtin_amdgcn_ballot_w64(mine && min3u(low, frac[2], frac[3]) < width8) != 0) {
+        // an integer (not zero: the sum is not negative) lies too near one of the
+        // sums: each lane evaluates its undecided cells one by one
+        uint32_t todo = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          todo |= mine && frac[i] < width8 && out[i] != 0 ? 1u << i : 0u;
+        // saturated and other flat areas are undecided everywhere: where the
+        // four windows hold one level the byte is the table's
+        const uint32_t* own = raw + wr * E::RP + wc / 4 + (mine ? rgrp : 0);
+        const uint32_t level = own[0] & 0xFFu, all4 = level * 0x01010101u;
+        uint32_t diff = 0;
+#pragma unroll
+        for (int y = 0; y < N; ++y)
+#pragma unroll
+          for (int q = 0; q < (N + 6) / 4; ++q) {
+            const uint32_t d = own[y * E::RP + q] ^ all4;
+            diff |= 4 * q + 4 <= N + 3 ? d : d & 0xFFFFu;  // N + 3 columns, an even number
+          }
+        if (todo != 0 && diff == 0) {
+          const uint32_t v = flat[level ^ 0x80u];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) out[q] = v;
+          todo = 0;
+        }
+        while (__builtin_amdgcn_ballot_w64(todo != 0) != 0) {
+          const int i = todo != 0 ? __builtin_ctz(todo) : 0;
+          // (a lane that is done reads its window's first columns)
+          const int col = todo != 0 ? wc + 4 * rgrp + i : wc, sh = col & 3;
+          const uint32_t* src = raw + wr * E::RP + col / 4;
+          // a window row's N bytes lie in at most three dwords
+          uint32_t d[N][3];
+#pragma unroll
+          for (int y = 0; y < N; ++y)
+#pragma unroll
+            for (int q = 0; q < (N > 5 ? 3 : 2); ++q) d[y][q] = src[y * E::RP + q] ^ 0x80808080u;
+          float blur = 0.0f;
+#pragma unroll
+          for (int y = 0; y < N; ++y) {
+            const uint32_t b0 = __builtin_amdgcn_alignbyte(d[y][1], d[y][0], sh);
+            const uint32_t b1 = N > 5 ? __builtin_amdgcn_alignbyte(d[y][2], d[y][1], sh)
+                                      : d[y][1] >> (8 * sh);
+#pragma unroll
+            for (int x = 0; x < N; ++x) {
+              const uint32_t byte = ((x < 4 ? b0 : b1) >> (8 * (x & 3))) & 0xFFu;
+              const float prod = float(byte) * w2[y * N + x];
+              blur = blur + prod;
+            }
+          }
+          const uint32_t v = uint32_t(__builtin_fminf(255.0f, blur));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) out[q] = todo != 0 && q == i ? v : out[q];
+          todo &= todo - 1;
+        }
+      }
+      if (mine) {
+        uint32_t* dst = gb + wr * E::GBP + wc + 4 * rgrp;
+        *reinterpret_cast<Vec<uint32_t, 4>*>(dst) = Vec<uint32_t, 4>{{out[0], out[1], out[2], out[3]}};
+      }
+    }
+    __syncthreads();
+
+    // 3. each pixel's median of the nine blurred bytes, then the 8-bit update
+    uint32_t xs[PX];
+    if constexpr (MED) {
+      uint32_t p[3][PX + 2];
+      if (inside) {
+        const uint32_t* nb = gb + ty * E::GBP + tx;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+          for (int d = 0; d < PX + 2; ++d) p[r][d] = nb[r * E::GBP + d];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+          for (int d = 0; d < PX + 2; ++d) p[r][d] = gb[gr[r] * E::GBP + gc[d]];
+      }
+      uint32_t lo[PX + 2], md[PX + 2], hi[PX + 2];
+#pragma unroll
+      for (int d = 0; d < PX + 2; ++d) {
+        lo[d] = min3u(p[0][d], p[1][d], p[2][d]);
+        md[d] = med3u(p[0][d], p[1][d], p[2][d]);
+        hi[d] = max3u(p[0][d], p[1][d], p[2][d]);
+      }
+#pragma unroll
+      for (int q = 0; q < PX; ++q)
+        xs[q] = med3u(max3u(lo[q], lo[q + 1], lo[q + 2]), med3u(md[q], md[q + 1], md[q + 2]),
+                      min3u(hi[q], hi[q + 1], hi[q + 2]));
+    } else {
+#pragma unroll
+      for (int q = 0; q < PX; ++q) xs[q] = gb[gr[1] * E::GBP + gc[q + 1]];
+    }
+
+    using Bytes = Vec<uint8_t, PX>;
+    Bytes none, fv;
+    const Bytes mk = __builtin_bit_cast(
+        Bytes, typename fwd::Raw<PX>::type(frame8<PX, true, false, PRINTED>(s, xs, var_init, tbl, none)));
+    const int64_t o = t * a.frame_stride + foff;
+    auto put = [&](uint8_t* out, const Bytes& v) {
+      if (vec_ok) {
+        *reinterpret_cast<Bytes*>(out + o) = v;
+      } else {
+#pragma unroll
+        for (int q = 0; q < PX; ++q)
+          if (valid[q]) out[o + q] = v.v[q];
+      }
+    };
+    put(a.masks, mk);
+    if (a.filtered) {
+#pragma unroll
+      for (int q = 0; q < PX; ++q) fv.v[q] = uint8_t(xs[q]);
+      put(static_cast<uint8_t*>(a.filtered), fv);
+    }
+  }
+
+  const Planes8<PX> b = pack8<PX>(s);
+#pragma unroll
+  for (int q = 0; q < PX; ++q) {
+    if (!valid[q]) continue;
+    planes[0][pix + q] = b.mA.v[q];
+    planes[1][pix + q] = b.vA.v[q];
+    planes[2][pix + q] = b.mC.v[q];
+    planes[3][pix + q] = b.vC.v[q];
+    a.age_a[pix + q] = b.aA.v[q];
+    a.age_c[pix + q] = b.aC.v[q];
+  }
+}
+
+// Half an ulp of a single-precision value up to v, in units of 2^-24.
+double half_ulp24(double v) { return std::exp2(std::floor(std::log2(v))); }
+
+// Whether the window's weights fit the fixed-point form, and how far (in units
+// of 2^-24) the appendix's single-precision sum can lie above the fixed-point
+// one, and from its lowest to its highest: the weights' rounding at all pixels
+// whose weight was rounded down (up), and half an ulp of every product and of
+// every partial sum, which are largest with all pixels at 255 (the rounding of
+// a sum grows with it).
+bool blur_fits(const double* w, int n, uint32_t* above, uint32_t* width) {
+  double total = 0.0, down = 0.0, up = 0.0, chain = 0.0;
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j) {
+      const double v = double(float(w[i] * w[j]));
+      if (!(v >= 0.0) || v > 0.49) return false;  // three signed bytes of 2^-24
+      const double off = v * 16777216.0 - std::rint(v * 16777216.0);
+      (off > 0.0 ? down : up) += std::fabs(off);
+      total += v;
+      if (v > 0.0) chain += half_ulp24(255.001 * v);
+      if (total > v) chain += half_ulp24(255.001 * total);  // the first sum is the product itself
+    }
+  if (total > 1.003) return false;  // 255 * total + above stays below 256
+  *above = uint32_t(std::ceil(255.0 * down + 1.0001 * chain)) + 1u;
+  *width = *above + uint32_t(std::ceil(255.0 * up + 1.0001 * chain)) + 1u;
+  return *width < (1u << 20);
+}
+
+template <int RG, bool MED, bool PRINTED>
+hipError_t launch_pre_mfma(PreArgs a, hipStream_t stream) {
+  using geom::pre::Small;
+  using geom::pre::Wide;
+  auto go = [&](auto tile, auto kernel) {
+    using Tile = decltype(tile);
+    a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
+    a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
+    hipLaunchKernelGGL(kernel, dim3(uint32_t(a.tiles_x * a.tiles_y)), dim3(geom::pre::NT), 0, stream, a);
+    return hipGetLastError();
+  };
+  if (a.tiles_x * a.tiles_y < SMALL8_BELOW)  // tiles of 16 x 64 (the caller's count)
+    return go(Small{}, pre_u8_mfma_kernel<RG, MED, PRINTED, Small>);
+  return go(Wide{}, pre_u8_mfma_kernel<RG, MED, PRINTED, Wide>);
+}
+
 template <bool MED, bool PRINTED>
-hipError_t launch_pre_rg(const PreArgs& a, int rg, hipStream_t stream) {
+hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
   const dim3 grid{uint32_t(a.tiles_x * a.tiles_y), 1, 1}, block{geom::pre::NT, 1, 1};
-  switch (rg) {
+  // (decision codes, a debug output, exist on pre_u8_kernel only)
+  const bool fits = rg > 0 && !a.codes && blur_fits(a.w, 2 * rg + 1, &a.blur_above, &a.blur_width);
+  switch (fits ? rg + 4 : rg) {
     case 0: hipLaunchKernelGGL((pre_u8_kernel<0, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 1: hipLaunchKernelGGL((pre_u8_kernel<1, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 2: hipLaunchKernelGGL((pre_u8_kernel<2, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 3: hipLaunchKernelGGL((pre_u8_kernel<3, MED, PRINTED>), grid, block, 0, stream, a); break;
+    case 5: return launch_pre_mfma<1, MED, PRINTED>(a, stream);
+    case 6: return launch_pre_mfma<2, MED, PRINTED>(a, stream);
+    case 7: return launch_pre_mfma<3, MED, PRINTED>(a, stream);
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -253,6 +253,69 @@ def test_u8_filtered_edge_shapes(T, H, W):
     _u8_check(out, dst, x, st, p, 5, 1)
 
 
+def _u8_content(kind, T, H, W):
+    rng = np.random.default_rng(61)
+    if kind == "noise":
+        return rng.integers(0, 256, (T, H, W)).astype(np.uint8)
+    # flat patches of every level, black and white among them: window sums at or
+    # next to integers, where the fixed-point sum does not decide the byte
+    levels = rng.permutation(256).astype(np.uint8)
+    levels[:8] = (0, 255, 0, 255, 0, 255, 1, 254)
+    y, x = np.mgrid[0:H, 0:W]
+    return np.stack([levels[((y // 9) * 31 + x // 11 + t) % 256] for t in range(T)])
+
+
+@pytest.mark.parametrize("kind", ["noise", "flat"])
+@pytest.mark.parametrize("H,W", [(37, 150), (365, 1461), (365, 1464), (5, 3)])
+@pytest.mark.parametrize("n,median,sigma", [(3, 1, 1.0), (5, 1, 1.0), (7, 1, 1.0), (5, 0, 0.8),
+                                            (7, 0, 2.5), (3, 0, 0.6), (5, 1, 0.3)])
+def test_u8_filtered_blur_in_fixed_point(kind, H, W, n, median, sigma):
+    """Calls without decision codes form the blur sums in fixed point on the
+    matrix cores (small and large frames' tiles, ragged and aligned widths;
+    sigma 0.3 has a weight too large for it): the appendix's bytes all the same."""
+    T = 3
+    x = _u8_content(kind, T, H, W)
+    _, st = _u8_case(62, 1, H, W)
+    p = dsgm.dsgm_params_default(255.0, 1)
+    dst = _u8_state(st, H, W)
+    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), dst, p,
+                                dsgm.gauss_filter(n, sigma, median), filtered=True)
+    torch.cuda.synchronize()
+    xf = oracle.preprocess_u8(x, oracle.gauss_weights(n, sigma), median=bool(median))
+    G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
+    ref = oracle.forward_u8(xf.reshape(T, -1), st, G.oracle_params(p))
+    G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.int64), ref["masks"].astype(np.int64))
+    for k in ("mean_a", "var_a", "mean_c", "var_c", "age_a", "age_c"):
+        G.assert_bit_exact(k, getattr(dst, k).cpu().numpy().ravel().astype(np.int64),
+                           ref[k].astype(np.int64))
+
+
+@pytest.mark.parametrize("weights", [[0.1, 0.2, 0.3, 0.15, 0.2], [0.0, 0.0, 0.45, 0.0, 0.5],
+                                     [-0.1, 0.3, 0.6, 0.3, -0.1], [0.4, 0.4, 0.4, 0.4, 0.4]])
+def test_u8_filtered_callers_weights(weights):
+    """Taps of the caller's own: asymmetric and with zeros (fixed point),
+    negative or summing to more than one (single precision throughout)."""
+    T, H, W, n = 3, 45, 131, 5
+    x = _u8_content("noise", T, H, W)
+    _, st = _u8_case(63, 1, H, W)
+    p = dsgm.dsgm_params_default(255.0, 1)
+    filt = dsgm.gauss_filter(n, 1.0, True)
+    for i, v in enumerate(weights):
+        filt.weights[i] = v
+    dst = _u8_state(st, H, W)
+    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), dst, p, filt, filtered=True)
+    ref_dst = _u8_state(st, H, W)  # with codes: the single-precision kernel
+    ref = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), ref_dst, p, filt, filtered=True,
+                                codes=True)
+    torch.cuda.synchronize()
+    assert torch.equal(out["filtered"], ref["filtered"]) and torch.equal(out["masks"], ref["masks"])
+    for a, b in zip(dst.planes(), ref_dst.planes()):
+        assert torch.equal(a, b)
+    if min(weights) >= 0:
+        xf = oracle.preprocess_u8(x, np.array(weights), median=True)
+        G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
+
+
 def test_u8_filtered_strided_frames_and_rejections():
     """A padded view of the frames (scalar stores), and the argument checks of
     the 8-bit pairing."""
