@@ -584,10 +584,17 @@ def backward(frames: torch.Tensor, params: Params, ckpt: torch.Tensor, ckpt_ever
 
 
 def _like_frames(t, frames, dtype):
-    """t (or zeros) in the frames' layout and the given dtype."""
-    out = torch.empty_strided(frames.shape, frames.stride(), dtype=dtype, device=frames.device)
+    """t (None for zeros) in the frames' layout and the given dtype: t itself
+    where it has them, else a copy (an upstream gradient of 128 x 480 x 640
+    FP32 values takes 59 us to copy, half of its backward kernel's time)."""
     if t is None:
         return None
+    if (type(t) is torch.Tensor and t.layout == torch.strided and t.dtype == dtype
+            and t.device == frames.device and t.shape == frames.shape and not t.is_neg()
+            and not t._is_zerotensor() and t.data_ptr() % t.element_size() == 0
+            and all(n <= 1 or a == b for n, a, b in zip(t.shape, t.stride(), frames.stride()))):
+        return t
+    out = torch.empty_strided(frames.shape, frames.stride(), dtype=dtype, device=frames.device)
     out.copy_(t)
     return out
 
@@ -621,6 +628,9 @@ class DSGMFunction(torch.autograd.Function):
         ctx.params, ctx.K, ctx.acc = p, ckpt_every, acc
         ctx.var_init_like = var_init if torch.is_tensor(var_init) else None
         ctx.mark_non_differentiable(out["masks"], st.age_a, st.age_c)
+        # no zeros in the place of gradients that are not there (the masks' and
+        # ages' never are): backward() takes None for zero
+        ctx.set_materialize_grads(False)
         return (out["masks"], out["bg"], st.mean_a, st.var_a, st.mean_c, st.var_c, st.age_a,
                 st.age_c)
 
@@ -631,8 +641,8 @@ class DSGMFunction(torch.autograd.Function):
         gbg = _like_frames(g_bg, frames, adt)
         gsT = None
         if any(g is not None for g in (g_mA, g_vA, g_mC, g_vC)):
-            ref = frames.new_zeros((frames.shape[1], frames.shape[2]), dtype=adt)
-            gsT = tuple((g if g is not None else ref).to(adt).contiguous()
+            zero = lambda: frames.new_zeros((frames.shape[1], frames.shape[2]), dtype=adt)
+            gsT = tuple((zero() if g is None else g).to(adt).contiguous()
                         for g in (g_mA, g_vA, g_mC, g_vC))
         r = backward(frames, ctx.params, ckpt, ctx.K, ctx.acc, gbg, gsT)
         gx = r["grad_frames"].to(frames.dtype)

@@ -184,6 +184,46 @@ def test_autograd_function_matches_direct_calls():
     assert torch.equal(mA.detach(), st.mean_a)
 
 
+@pytest.mark.parametrize("layout", ["expanded", "permuted", "padded", "negated"])
+def test_autograd_upstream_layouts(layout):
+    """An upstream gradient in the frames' layout is used as it is, any other is
+    copied: the same values give the same gradients, and the upstream itself
+    is not written.  Frames are a padded view, so the layout is not the dense one."""
+    T, H, W = 11, 6, 20
+    p = dsgm.dsgm_params_default(2.0)
+    fr, st = G.device_case(33, T, H, W, torch.float32, torch.float32)
+    big = torch.zeros((T, H + 1, W + 4), device="cuda")
+    x0 = big[:, :H, :W].copy_(fr)
+    vals = torch.randn((T, H, W), device="cuda")
+    if layout == "expanded":
+        vals = torch.randn((1, 1, W), device="cuda").expand(T, H, W)
+    like = torch.empty((T, H + 1, W + 4), device="cuda")[:, :H, :W].copy_(vals)
+    assert like.stride() == x0.stride()
+    other = {"expanded": lambda: vals,
+             "permuted": lambda: vals.permute(2, 1, 0).contiguous().permute(2, 1, 0),
+             "padded": lambda: torch.empty((T, H + 2, W + 8), device="cuda")[:, :H, :W].copy_(vals),
+             "negated": lambda: torch._neg_view(-like)}[layout]()
+    before = like.clone()
+
+    def grads(g, gm):
+        x = x0.detach().requires_grad_()
+        vi = torch.tensor(p.var_init, dtype=torch.float64, device="cuda", requires_grad=True)
+        out = dsgm.DSGMFunction.apply(x, *st.planes(), vi, p, 4)
+        torch.autograd.backward([o for o, u in ((out[1], g), (out[2], gm)) if u is not None],
+                                [u for u in (g, gm) if u is not None])
+        return x.grad, vi.grad
+
+    gm = torch.randn((H, W), device="cuda")
+    for a, b in zip(grads(like, gm), grads(other, gm)):
+        assert torch.equal(a, b)
+    assert torch.equal(like, before)
+    zero = torch.zeros_like
+    for a, b in zip(grads(like, None), grads(like, zero(gm))):  # an absent gradient is zero
+        assert torch.equal(a, b)
+    for a, b in zip(grads(None, gm), grads(zero(like), gm)):
+        assert torch.equal(a, b)
+
+
 def test_torch_gradcheck_tiny():
     """torch.autograd.gradcheck on a tiny FP64 instance whose decision margins
     are all far from zero (so +-eps never flips a decision)."""
