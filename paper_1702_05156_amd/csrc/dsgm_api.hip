@@ -180,7 +180,7 @@ int preferred_vector(int in_dtype, int acc) {
 int filling_vector(int64_t px, int P, int acc) {
   constexpr int64_t kSimds = 1024;
   const int64_t need = (acc == DSGM_ACC_F32 || acc == DSGM_ACC_U8 ? 3 : 2) * kSimds;
-  while (P > 1 && px / (64 * P) < need) P /= 2;
+  while (P > 1 && px < need * 64 * P) P /= 2;
   return P;
 }
 

@@ -642,6 +642,7 @@ struct Geo8 {
   static constexpr int WIN = G::GB_H * CG;                 // windows of a tile
   static constexpr int GROUPS = (WIN + 15) / 16;
   static constexpr int SETS = N > 4 ? 2 : 1;               // products per group and digit
+  static_assert(4 * SETS > N, "a row of zeros");
   static_assert(OW + N - 1 <= 16 && OW % 4 == 0, "a window's outputs read its 16 bytes");
 };
 
@@ -687,42 +688,51 @@ __global__ void __launch_bounds__(geom::pre::NT)
   __shared__ alignas(16) uint32_t gb[G::GB_H * E::GBP];    // blurred bytes, one to a dword
   __shared__ Tables8 tbl;
   __shared__ float wf[N * N];
+  // the weights' digits as bytes, a window row at byte 16 of a row of zeros
+  __shared__ uint32_t digits[3][4 * E::SETS][9];
+  __shared__ int32_t centre128;  // 128 times the sum of the fixed-point weights
   __shared__ uint32_t flat[256];  // the blurred byte of a window of one level
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const StepConsts<double> k =
       make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
-  for (int e = tid; e < N * N; e += NT) wf[e] = window_weight<N>(a.w, e);
+  for (int i = tid; i < int(sizeof(digits) / 4); i += NT) (&digits[0][0][0])[i] = 0u;
+  if (tid == 0) centre128 = 0;
+  __syncthreads();
+  for (int e = tid; e < N * N; e += NT) {
+    const float w = window_weight<N>(a.w, e);
+    const int32_t W = fixed24(w);
+    const int32_t d0 = int8_t(W), W1 = (W - d0) >> 8, d1 = int8_t(W1), d2 = (W1 - d1) >> 8;
+    const int32_t d[3] = {d0, d1, d2};
+    wf[e] = w;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      reinterpret_cast<int8_t*>(digits[q][e / N])[16 + e % N] = int8_t(d[q]);
+    atomicAdd(&centre128, 128 * W);
+  }
   fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
   const uint32_t var_init = uint32_t(a.var_init);
 
   // A: output m = lane % 16, row group lane / 16, byte j: the weight's digit of
-  // window row dy, window column j - m
+  // window row dy, window column j - m (formed once a weight and read shifted:
+  // every lane converting its own 32 bytes cost as much as the frames of a short
+  // call)
   const int m = lane & 15, rgrp = lane >> 4;
   V4 A[E::SETS][3];
 #pragma unroll
   for (int st = 0; st < E::SETS; ++st)
 #pragma unroll
-    for (int dw = 0; dw < 4; ++dw) {
-      uint32_t dig[3] = {0u, 0u, 0u};
+    for (int q = 0; q < 3; ++q) {
+      // bytes 16 - m .. 31 - m of the row (row N is zero, for lanes without an output)
+      const uint32_t* row = digits[q][m < E::OW ? 4 * st + rgrp : N] + (16 - m) / 4;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int j = 4 * dw + b, dy = 4 * st + rgrp;
-        const bool in = dy < N && j >= m && j - m < N && m < E::OW;
-        const int32_t W = in ? fixed24(wf[dy * N + j - m]) : 0;
-        const int32_t d0 = int8_t(W), W1 = (W - d0) >> 8, d1 = int8_t(W1), d2 = (W1 - d1) >> 8;
-        dig[0] |= uint32_t(d0 & 0xFF) << (8 * b);
-        dig[1] |= uint32_t(d1 & 0xFF) << (8 * b);
-        dig[2] |= uint32_t(d2 & 0xFF) << (8 * b);
-      }
-#pragma unroll
-      for (int q = 0; q < 3; ++q) A[st][q][dw] = int32_t(dig[q]);
+      for (int dw = 0; dw < 4; ++dw)
+        A[st][q][dw] = int32_t(__builtin_amdgcn_alignbyte(row[dw + 1], row[dw], uint32_t(-m) & 3u));
     }
   // the bytes are staged less 128: the sum gets 128 times the weights back
   // and the sum's upper end is what is formed: its integer part is the result's
   // unless the integer lies less than blur_width below it
-  int32_t centre = int32_t(a.blur_above);
-  for (int e = 0; e < N * N; ++e) centre += 128 * fixed24(wf[e]);
+  const int32_t centre = int32_t(a.blur_above) + centre128;
   const uint32_t width8 = a.blur_width << 8;  // compared with the fraction in the top 24 bits
   float w2[N * N];  // the window's weights in scalar registers
 #pragma unroll
@@ -730,8 +740,9 @@ __global__ void __launch_bounds__(geom::pre::NT)
     w2[e] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wf[e])));
   for (int c = tid; c < 256; c += NT) {  // (read after the frame loop's first barrier)
     float blur = 0.0f;
+#pragma unroll
     for (int e = 0; e < N * N; ++e) {
-      const float prod = float(c) * wf[e];
+      const float prod = float(c) * w2[e];
       blur = blur + prod;
     }
     flat[c] = uint32_t(__builtin_fminf(255.0f, blur));
@@ -1025,7 +1036,14 @@ template <bool MED, bool PRINTED>
 hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
   const dim3 grid{uint32_t(a.tiles_x * a.tiles_y), 1, 1}, block{geom::pre::NT, 1, 1};
   // (decision codes, a debug output, exist on pre_u8_kernel only)
-  const bool fits = rg > 0 && !a.codes && blur_fits(a.w, 2 * rg + 1, &a.blur_above, &a.blur_width);
+  // A short call on a large frame doesn't pay for the matrix kernel's fragments and
+  // its tiles of half the size.  pre_u8_kernel / pre_u8_mfma_kernel, us, T x 1080
+  // x 1920: 5 taps 26.3 / 29.8 (T = 1), 36.4 / 35.6 (2), 52.6 / 47.7 (4); 3 taps
+  // 23.9 / 25.8, 32.3 / 32.0, 46.1 / 42.0; 7 taps 67.4 / 70.2 (4), 94.2 / 88.6 (6).
+  // 7 taps at 4 x 240 x 320, in 8 x 32 tiles: 18.8 / 14.0.
+  const bool pays = a.T >= (rg < 3 ? 2 : 5) || a.tiles_x * a.tiles_y < SMALL8_BELOW;
+  const bool fits = rg > 0 && pays && !a.codes &&
+                    blur_fits(a.w, 2 * rg + 1, &a.blur_above, &a.blur_width);
   switch (fits ? rg + 4 : rg) {
     case 0: hipLaunchKernelGGL((pre_u8_kernel<0, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 1: hipLaunchKernelGGL((pre_u8_kernel<1, MED, PRINTED>), grid, block, 0, stream, a); break;

@@ -290,6 +290,25 @@ def test_u8_filtered_blur_in_fixed_point(kind, H, W, n, median, sigma):
                            ref[k].astype(np.int64))
 
 
+@pytest.mark.parametrize("T", [1, 2, 4, 5])
+@pytest.mark.parametrize("n", [3, 5, 7])
+def test_u8_filtered_call_lengths(n, T):
+    """Short calls on a large frame sum the windows in single precision, longer
+    ones on the matrix cores: the line lies between these lengths."""
+    H, W = 364, 1463
+    x = _u8_content("flat", T, H, W)
+    _, st = _u8_case(64, 1, H, W)
+    p = dsgm.dsgm_params_default(255.0, 1)
+    dst = _u8_state(st, H, W)
+    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), dst, p,
+                                dsgm.gauss_filter(n, 1.0, True), filtered=True)
+    torch.cuda.synchronize()
+    xf = oracle.preprocess_u8(x, oracle.gauss_weights(n, 1.0), median=True)
+    G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
+    ref = oracle.forward_u8(xf.reshape(T, -1), st, G.oracle_params(p))
+    G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.int64), ref["masks"].astype(np.int64))
+
+
 @pytest.mark.parametrize("weights", [[0.1, 0.2, 0.3, 0.15, 0.2], [0.0, 0.0, 0.45, 0.0, 0.5],
                                      [-0.1, 0.3, 0.6, 0.3, -0.1], [0.4, 0.4, 0.4, 0.4, 0.4]])
 def test_u8_filtered_callers_weights(weights):
