@@ -153,6 +153,16 @@ struct Model {
   int aA, aC;  // ages as table offsets (age_in)
 };
 
+// Converts ages that were loaded as bytes, at this point and no earlier
+// (volatile): the conversion waits for the loads, so a kernel requests its
+// first frames before it.
+template <typename Acc>
+__device__ __forceinline__ void convert_ages(Model<Acc>& s) {
+  asm volatile("" : "+v"(s.aA), "+v"(s.aC));
+  s.aA = age_in<Acc>(s.aA);
+  s.aC = age_in<Acc>(s.aC);
+}
+
 // What one step decided, for the reverse sweep: the table offset used (of the
 // matched model's age, or of RESET_SLOT), whether A matched, whether C was promoted,
 // and d = (updated mean) - x of the blend.

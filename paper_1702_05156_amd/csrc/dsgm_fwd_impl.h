@@ -169,11 +169,7 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       s[q] = pre[q];
-      // (volatile: the conversions stay after the table's barrier, where the
-      // ages have arrived)
-      asm volatile("" : "+v"(s[q].aA), "+v"(s[q].aC));
-      s[q].aA = age_in<Acc>(s[q].aA);
-      s[q].aC = age_in<Acc>(s[q].aC);
+      convert_ages(s[q]);  // (after the table's barrier, where the ages have arrived)
     }
   } else {
     // load_state's loads written out rather than called: a call compiles
@@ -192,8 +188,8 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
       s[q].vA = vA.v[q];
       s[q].mC = mC.v[q];
       s[q].vC = vC.v[q];
-      s[q].aA = age_in<Acc>(aA.v[q]);
-      s[q].aC = age_in<Acc>(aC.v[q]);
+      s[q].aA = aA.v[q];  // (converted once the first frames are requested)
+      s[q].aC = aC.v[q];
     }
   }
 
@@ -282,6 +278,8 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
   const int64_t nfull = T / U;
   Vec<In, P> xa[U], xb[U];
   if (nfull > 0) load_batch(xa, 0);
+#pragma unroll
+  for (int q = 0; q < P; ++q) convert_ages(s[q]);
   for (int64_t b = 0; b < nfull; b += 2) {
     if (b + 1 < nfull) load_batch(xb, (b + 1) * U);
     run_batch(xa, b * U);
