@@ -37,9 +37,37 @@ constexpr int bwd_waves() {
 }
 
 // The frames, the upstream gradients and the gradients of the frames pass
-// through once: nontemporal (FP32 state 112 against 119 us on 128 frames of
-// 480 x 640, FP64 state 632 against 650 us on the frames above).
-template <typename In, typename Acc, typename Io, int KC, bool HAS_GBG, bool HAS_GST>
+// through once: nontemporal (NT; FP32 state 112 against 119 us on 128 frames of
+// 480 x 640, FP64 state 632 against 650 us on the frames above), if wavefronts
+// touch whole cache lines.  Where frames begin inside a line, two wavefronts
+// share it, and a nontemporal one has left the cache before the second comes:
+// FP32 state, 32 x 721 x 1279, 125 against 102 us with plain accesses.  Arrays
+// that fit the 256 MiB last-level cache are also left to it (32 x 480 x 640, 118
+// MB: 36.5 nontemporal, 34.3 us plain).
+template <typename X, bool NT>
+__device__ __forceinline__ X ld1(const char* p) {
+  if constexpr (NT) return fwd::ld_stream<X, 1>(reinterpret_cast<const X*>(p)).v[0];
+  return *reinterpret_cast<const X*>(p);
+}
+template <typename X, bool NT>
+__device__ __forceinline__ void st1(char* p, X v) {
+  if constexpr (NT)
+    fwd::st_stream<X, 1>(reinterpret_cast<X*>(p), Vec<X, 1>{{v}});
+  else
+    *reinterpret_cast<X*>(p) = v;
+}
+bool streams(const BwdArgs& a, int64_t in, int64_t io) {
+  constexpr int64_t LINE = 128, CACHE = int64_t(256) << 20;
+  if (a.T * a.H * a.W * (in + (a.grad_bg ? 2 : 1) * io) < CACHE) return false;
+  const int64_t n = in < io ? in : io;  // (a multiple of LINE for the narrower is one for both)
+  const uintptr_t bases = reinterpret_cast<uintptr_t>(a.frames) |
+                          reinterpret_cast<uintptr_t>(a.grad_bg) |
+                          reinterpret_cast<uintptr_t>(a.grad_frames);
+  return bases % LINE == 0 && (a.T <= 1 || a.frame_stride * n % LINE == 0) &&
+         (a.row_stride == a.W || a.row_stride * n % LINE == 0);
+}
+
+template <typename In, typename Acc, typename Io, int KC, bool HAS_GBG, bool HAS_GST, bool NT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bwd_waves<Acc>())))
 bwd_kernel(const BwdArgs a) {
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
@@ -96,8 +124,7 @@ bwd_kernel(const BwdArgs a) {
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (ALL || i < len)
-        xs[i] = fwd::ld_stream<In, 1>(
-            reinterpret_cast<const In*>(frames + (c0 + i) * fs_in + off_in)).v[0];
+        xs[i] = ld1<In, NT>(frames + (c0 + i) * fs_in + off_in);
     // the upstream gradients are requested in the order the sweep uses them,
     // last frame first: one after each replayed frame (EARLY: FP64 arrays and
     // F32X2 state), or those of frames [LATE, N) after the replay and [0, LATE)
@@ -107,8 +134,7 @@ bwd_kernel(const BwdArgs a) {
     auto load_gb = [&](const int j) {
       gb[j] = Io(0);
       if (HAS_GBG && (ALL || j < len))
-        gb[j] = fwd::ld_stream<Io, 1>(
-            reinterpret_cast<const Io*>(gbg + (c0 + j) * fs_io + off_io)).v[0];
+        gb[j] = ld1<Io, NT>(gbg + (c0 + j) * fs_io + off_io);
     };
     Acc tape_d[N];
     uint32_t tape_m[(N + 1) / 2];
@@ -141,8 +167,7 @@ bwd_kernel(const BwdArgs a) {
         const int idx = int(m & 0xFFF0u);
         const Acc gx = reverse_step<Acc, HAS_GBG>(adj, Acc(gb[i]), tape_d[i], idx, (m & 1u) != 0,
                                                   (m & 2u) != 0, entry_at(tbl, idx));
-        fwd::st_stream<Io, 1>(reinterpret_cast<Io*>(gfr + (c0 + i) * fs_io + off_io),
-                              Vec<Io, 1>{{Io(gx)}});  // rounded once
+        st1<Io, NT>(gfr + (c0 + i) * fs_io + off_io, Io(gx));  // rounded once
       }
     }
   };
@@ -277,20 +302,29 @@ __global__ void __launch_bounds__(RED_THREADS) reduce_pass2(const double* __rest
   if (threadIdx.x == 0) out[0] = sh[0].s + sh[0].c;
 }
 
-template <typename In, typename Acc, typename Io, int KC>
-hipError_t launch_bwd_k(const BwdArgs& a, hipStream_t stream) {
+template <typename In, typename Acc, typename Io, int KC, bool NT>
+hipError_t launch_bwd_nt(const BwdArgs& a, hipStream_t stream) {
   const int block = 256;
-  const int64_t grid = (a.H * a.W + block - 1) / block;
+  const dim3 grid(uint32_t((a.H * a.W + block - 1) / block));
   const bool gb = a.grad_bg != nullptr, gs = a.gst_mean_a != nullptr;
   if (gb && gs)
-    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, true, true>), dim3(uint32_t(grid)), dim3(block), 0, stream, a);
+    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, true, true, NT>), grid, dim3(block), 0, stream, a);
   else if (gb)
-    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, true, false>), dim3(uint32_t(grid)), dim3(block), 0, stream, a);
+    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, true, false, NT>), grid, dim3(block), 0, stream, a);
   else if (gs)
-    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, false, true>), dim3(uint32_t(grid)), dim3(block), 0, stream, a);
+    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, false, true, NT>), grid, dim3(block), 0, stream, a);
   else
-    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, false, false>), dim3(uint32_t(grid)), dim3(block), 0, stream, a);
+    hipLaunchKernelGGL((bwd_kernel<In, Acc, Io, KC, false, false, NT>), grid, dim3(block), 0, stream, a);
   return hipGetLastError();
+}
+
+template <typename In, typename Acc, typename Io, int KC>
+hipError_t launch_bwd_k(const BwdArgs& a, hipStream_t stream) {
+  if constexpr (!is_f32x2<Acc>::value) {  // (bound by its arithmetic: no difference)
+    if (streams(a, sizeof(In), sizeof(Io)))
+      return launch_bwd_nt<In, Acc, Io, KC, true>(a, stream);
+  }
+  return launch_bwd_nt<In, Acc, Io, KC, false>(a, stream);
 }
 
 }  // namespace

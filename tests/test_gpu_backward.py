@@ -184,6 +184,28 @@ def test_autograd_function_matches_direct_calls():
     assert torch.equal(mA.detach(), st.mean_a)
 
 
+@pytest.mark.parametrize("H,W", [(720, 1280), (719, 1279)])
+def test_gradients_of_arrays_beyond_the_cache(H, W):
+    """Arrays of more than 256 MiB whose frames begin on cache lines are passed
+    through it, others not: the same gradients as the same pixels in a small
+    array's."""
+    T, rows = 28, 8
+    p = dsgm.dsgm_params_default(2.0)
+    fr, st = G.device_case(34, T, H, W, torch.float32, torch.float32)
+    g = torch.randn((T, H, W), device="cuda")
+
+    def grads(x, s, g):
+        s = dsgm.State(*(t.clone() for t in s.planes()))
+        out = dsgm.forward(x, s, p, bg=True, ckpt_every=16)
+        r = dsgm.backward(x, p, out["ckpt"], 16, dsgm.ACC_F32, g)
+        return [r["grad_frames"], *r["grad_state0"]]
+
+    part = dsgm.State(*(t.reshape(H, W)[:rows].contiguous() for t in st.planes()))
+    small = grads(fr[:, :rows].contiguous(), part, g[:, :rows].contiguous())
+    for a, b in zip(grads(fr, st, g), small):
+        assert torch.equal(a[..., :rows, :], b)
+
+
 @pytest.mark.parametrize("layout", ["expanded", "permuted", "padded", "negated"])
 def test_autograd_upstream_layouts(layout):
     """An upstream gradient in the frames' layout is used as it is, any other is
