@@ -158,9 +158,10 @@ constexpr int kTuneFlags = DSGM_TUNE_BG | DSGM_TUNE_CKPT | DSGM_TUNE_PRINTED;
 constexpr int kTuneFrames = 64;  // frames per timed call: the cost per frame is flat beyond
 constexpr int kTuneCkptEvery = 32;
 
-// Preferred pixels per lane, measured on MI355X at 1920x2560x500: FP64 and
-// FP32 state run fastest with 2 (more waves per SIMD), BF16 frames with 4
-// (wider loads of the narrow frames).
+// Preferred pixels per lane of frames that fill the chip (filling_vector narrows
+// them for others), measured at 1920x2560x500: FP64 and FP32 state run fastest
+// with 2 (more waves per SIMD), BF16 frames with 4 (wider loads of the narrow
+// frames).
 int preferred_vector(int in_dtype, int acc) {
   if (in_dtype == DSGM_IN_BF16) return 4;
   (void)acc;

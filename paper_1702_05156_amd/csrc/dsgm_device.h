@@ -2,7 +2,7 @@
 //
 // One step of the Dual-Mode Single Gaussian Model for one pixel (Henderson &
 // Vertescher, arXiv:1702.05156, Sec. 2.2-2.3 and the appendix's inner update),
-// written branch-free for 64-wide wavefronts:
+// written for 64-wide wavefronts, the selected model updated in place under lane masks:
 //
 //   match tests   hitA = (x-mA)^2 < ts*max(vA, vf); hitC = (x-mC)^2 < ts*max(vC, vf)
 //                 (evaluated as two comparisons, see step_core())

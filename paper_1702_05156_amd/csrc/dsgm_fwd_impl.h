@@ -389,9 +389,8 @@ __device__ __forceinline__ T wave_uniform(const T& v) {
 }
 
 // Waves per SIMD the batched kernel is compiled for.  BF16 frames with FP32
-// state, 4 pixels per lane and no bg output: 5 (96 instead of 104 VGPRs, a
-// 36-byte spill outside the frame loop), measured 2.4 % faster than 4; the
-// other variants spill more under that bound and keep the compiler's choice.
+// state, 4 pixels per lane and no bg output: 5 (90 VGPRs); the other variants
+// keep the compiler's choice.
 template <typename In, typename Acc, int P, int FLAGS>
 constexpr int batched_waves() {
   return (sizeof(In) == 2 && sizeof(Acc) == 4 && P == 4 && (FLAGS & F_BG) == 0) ? 5 : 1;

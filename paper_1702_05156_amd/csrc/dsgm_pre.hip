@@ -228,10 +228,6 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
       if (G::raw_active(tid, l)) nxt[l] = f[roff[l]];
   };
   if (a.T > 0) load_frame(0);
-  // (one frame of 1920 x 2560, FP64: 102 us with the ages converted as they are
-  // loaded, pixel by pixel)
-#pragma unroll
-  for (int q = 0; q < PX; ++q) convert_ages(s[q]);
 
   for (int64_t t = 0; t < a.T; ++t) {
     // 1. stage the raw tile, then start loading the next frame's
@@ -240,6 +236,11 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
       if (G::raw_active(tid, l)) buf_raw[G::raw_cell(tid, l)] = to_acc<In, Acc>(nxt[l]);
     __syncthreads();
     if (t + 1 < a.T) load_frame(t + 1);
+    if (t == 0) {  // the state has arrived (one frame of 1920 x 2560, FP64: 102 us with
+                   // the ages converted as they are loaded, pixel by pixel)
+#pragma unroll
+      for (int q = 0; q < PX; ++q) convert_ages(s[q]);
+    }
 
     const Acc* gbp;  // the blurred tile, GB_H x GB_W
     if constexpr (RG > 0) {
