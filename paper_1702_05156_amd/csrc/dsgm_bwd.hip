@@ -211,21 +211,15 @@ bwd_kernel(const BwdArgs a) {
         // code being too large for the instruction cache as it is
         piece(state_at(ch.lo), ch.lo, len, Whole{}, std::true_type{});
       } else {
-        // a shorter chunk is cut into pieces whose lengths are the powers of
-        // two of its length, the longest first in time: a compile-time length
-        // needs no guard (FP32 state spilled 80 registers with guards)
-        int64_t c0 = ch.hi;
-        auto part = [&](auto n_tag) {
-          constexpr int N = decltype(n_tag)::value;
-          if ((len & N) == 0) return;
-          c0 -= N;
-          piece(state_at(c0), c0, N, n_tag, std::false_type{});
-        };
-        part(std::integral_constant<int, 1>{});
-        part(std::integral_constant<int, 2>{});
-        part(std::integral_constant<int, 4>{});
-        part(std::integral_constant<int, 8>{});
-        if constexpr (KC > 16) part(std::integral_constant<int, 16>{});
+        // a shorter chunk: its first half tape without guards, the rest with
+        // them (a whole guarded tape spilled 80 registers with FP32 state;
+        // pieces of powers of two replayed 98 frames of a chunk of 31:
+        // 31 x 1630 x 1168, FP32, 332 us)
+        constexpr int HALF = KC / 2;
+        using Half = std::integral_constant<int, HALF>;
+        const int rest = len >= HALF ? len - HALF : len;
+        if (rest > 0) piece(state_at(ch.hi - rest), ch.hi - rest, rest, Half{}, std::true_type{});
+        if (len >= HALF) piece(state_at(ch.lo), ch.lo, HALF, Half{}, std::false_type{});
       }
     }
   }
