@@ -174,10 +174,10 @@ int preferred_vector(int in_dtype, int acc) {
 // instructions take longer to issue) the chain's latency bounds the call, and
 // narrower lanes, of which there are more, are faster although they issue more
 // loads and stores.  Measured, pixels per lane 4 / 2 / 1: BF16 frames with FP32
-// state 500 x 240 x 320: 216 / 137 / 104 us, 200 x 480 x 640: 97 / 70 / 65 us,
-// 100 x 720 x 1280 (3,600 wavefronts at 4): 75 / 75 / 83 us; 8-bit 200 x 240 x
-// 320: 119 / 71 / 50 us; FP64 500 x 240 x 320: 252 / 152 / 123 us, 200 x 480 x
-// 640 (2,400 wavefronts at 2): 136 / 114 / 121 us.
+// state 500 x 240 x 320: 202 / 124 / 90 us, 200 x 480 x 640: 88 / 61 / 60 us,
+// 100 x 720 x 1280 (3,600 wavefronts at 4): 74 / 73 / 81 us; 8-bit 200 x 240 x
+// 320: 119 / 71 / 50 us; FP64 500 x 240 x 320: 225 / 124 / 108 us, 200 x 480 x
+// 640 (2,400 wavefronts at 2): 154 / 110 / 116 us.
 int filling_vector(int64_t px, int P, int acc) {
   constexpr int64_t kSimds = 1024;
   const int64_t need = (acc == DSGM_ACC_F32 || acc == DSGM_ACC_U8 ? 3 : 2) * kSimds;

@@ -207,7 +207,7 @@ bwd_kernel(const BwdArgs a) {
       if (len == KC) {
         piece(state_at(ch.lo), ch.lo, len, Whole{}, std::false_type{});
       } else if constexpr (is_f32x2<Acc>::value) {
-        // guarded frames: the pieces below made this form 15-20 % slower, its
+        // guarded frames: a second tape length made this form 15-20 % slower, its
         // code being too large for the instruction cache as it is
         piece(state_at(ch.lo), ch.lo, len, Whole{}, std::true_type{});
       } else {
