@@ -107,4 +107,16 @@ hipError_t launch_count_nonfinite(const void* frames, int in_dtype, const CountA
 // logical tile of workgroup b of nb, XCD-contiguous (dsgm_geom.h)
 using geom::tile_of;
 
+// The launch grid of a preprocessing kernel's tiles, and the tile of this
+// workgroup (-1: none; the same in all its lanes).
+inline dim3 tile_grid(const PreArgs& a) {
+  const int64_t n = a.tiles_x * a.tiles_y;
+  return dim3(uint32_t(geom::pre::grid_x(n)), uint32_t(geom::pre::grid_y(n)), 1);
+}
+__device__ __forceinline__ int64_t tile_here(const PreArgs& a) {
+  const int64_t n = a.tiles_x * a.tiles_y;
+  const int64_t b = geom::pre::workgroup(blockIdx.x, blockIdx.y, gridDim.x);
+  return b < n ? tile_of(b, n) : -1;
+}
+
 }  // namespace dsgm

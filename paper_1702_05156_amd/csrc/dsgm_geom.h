@@ -116,6 +116,14 @@ constexpr int PX = 4;    // pixels per lane (one row)
 constexpr int NT = 256;  // lanes per workgroup
 static_assert(TH * TW == NT * PX, "tile = lanes x pixels");
 
+// A grid dimension of 2^32 lanes or more is launched modulo 2^32, without an
+// error: beyond GRID_X workgroups (2^31 lanes; narrow frames of 2^26 rows) the
+// tiles go on in the grid's y, and the workgroups past the last tile have none.
+constexpr int64_t GRID_X = int64_t(1) << 23;
+DSGM_HD int64_t grid_x(int64_t tiles) { return min64(tiles, GRID_X); }
+DSGM_HD int64_t grid_y(int64_t tiles) { return (tiles + GRID_X - 1) / GRID_X; }
+DSGM_HD int64_t workgroup(int64_t bx, int64_t by, int64_t nx) { return by * nx + bx; }
+
 // A tile's rows, columns and pixels per lane.  Small frames take Small: more
 // workgroups, and a quarter of the work in each lane's chain per frame.
 struct Big {

@@ -152,6 +152,8 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
   __shared__ alignas(16) Acc buf_hb[RG > 0 ? G::HB_N : 1];
   __shared__ alignas(16) Acc buf_gb[RG > 0 ? G::GB_N : 1];
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
+  const int64_t tile = tile_here(a);
+  if (tile < 0) return;
   fill_table<Acc>(tbl, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
   const StepConsts<Acc> k =
       make_consts<Acc>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
@@ -160,7 +162,6 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
 #pragma unroll
   for (int i = 0; i < 2 * RG + 1; ++i) wt[i] = Acc(a.w[i]);
 
-  const int64_t tile = tile_of(blockIdx.x, gridDim.x);
   const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
   const int tid = threadIdx.x;
   const int ty = G::lane_row(tid), tx = G::lane_col(tid);  // this lane's row and first column
@@ -377,7 +378,7 @@ template <typename In, typename Acc, typename Io, bool MED, bool PRINTED, typena
 hipError_t launch_tile(PreArgs a, int rg, hipStream_t stream) {
   a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
   a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
-  const dim3 grid{uint32_t(a.tiles_x * a.tiles_y), 1, 1}, block{NT, 1, 1};
+  const dim3 grid = tile_grid(a), block{NT, 1, 1};
   switch (rg) {
     case 0: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 0, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
     case 1: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 1, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;

@@ -424,6 +424,8 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
   __shared__ float buf_raw[G::RAW_N];
   __shared__ float buf_gb[RG > 0 ? G::GB_N : 1];
   __shared__ Tables8 tbl;
+  const int64_t tile = tile_here(a);
+  if (tile < 0) return;
   const StepConsts<double> k =
       make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
   fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // var_init already stored
@@ -434,7 +436,6 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 #pragma unroll
     for (int j = 0; j < N; ++j) w2[i * N + j] = float(a.w[i] * a.w[j]);
 
-  const int64_t tile = tile_of(blockIdx.x, gridDim.x);
   const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
   const int tid = threadIdx.x;
   const int ty = G::lane_row(tid), tx = G::lane_col(tid);
@@ -692,6 +693,8 @@ __global__ void __launch_bounds__(geom::pre::NT)
   __shared__ uint32_t digits[3][4 * E::SETS][9];
   __shared__ int32_t centre128;  // 128 times the sum of the fixed-point weights
   __shared__ uint32_t flat[256];  // the blurred byte of a window of one level
+  const int64_t tile = tile_here(a);
+  if (tile < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const StepConsts<double> k =
@@ -748,7 +751,6 @@ __global__ void __launch_bounds__(geom::pre::NT)
     flat[c] = uint32_t(__builtin_fminf(255.0f, blur));
   }
 
-  const int64_t tile = tile_of(blockIdx.x, gridDim.x);
   const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
   const int ty = G::lane_row(tid), tx = G::lane_col(tid);
   const int64_t gy = y0 + ty;
@@ -1024,7 +1026,7 @@ hipError_t launch_pre_mfma(PreArgs a, hipStream_t stream) {
     using Tile = decltype(tile);
     a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
     a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
-    hipLaunchKernelGGL(kernel, dim3(uint32_t(a.tiles_x * a.tiles_y)), dim3(geom::pre::NT), 0, stream, a);
+    hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a);
     return hipGetLastError();
   };
   if (a.tiles_x * a.tiles_y < SMALL8_BELOW)  // tiles of 16 x 64 (the caller's count)
@@ -1034,7 +1036,7 @@ hipError_t launch_pre_mfma(PreArgs a, hipStream_t stream) {
 
 template <bool MED, bool PRINTED>
 hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
-  const dim3 grid{uint32_t(a.tiles_x * a.tiles_y), 1, 1}, block{geom::pre::NT, 1, 1};
+  const dim3 grid = tile_grid(a), block{geom::pre::NT, 1, 1};
   // (decision codes, a debug output, exist on pre_u8_kernel only)
   // A short call on a large frame doesn't pay for the matrix kernel's fragments and
   // its tiles of half the size.  pre_u8_kernel / pre_u8_mfma_kernel, us, T x 1080

@@ -1,0 +1,49 @@
+"""The fused preprocessing (dsgm_forward_filtered) at sizes and contents that
+select its other kernels and launch forms: grids of 2^32 lanes and more."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_1702_05156_amd import dsgm
+
+
+def _random(H, W, T, u8, seed):
+    """Frames, model state and parameters of random bytes (u8) or of BF16 frames
+    and FP32 state."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    byte = lambda *n, lo=0, hi=256: torch.randint(lo, hi, n, dtype=torch.uint8, device="cuda", generator=g)
+    x, planes = byte(T, H, W), [byte(H, W) for _ in range(4)]
+    if not u8:
+        x, planes = x.to(torch.bfloat16) / 256, [q.float() / 256 for q in planes]
+    return x, dsgm.State(*planes, byte(H, W, lo=1, hi=31), byte(H, W, lo=1, hi=31)), \
+        dsgm.dsgm_params_default(255.0 if u8 else 1.0)
+
+
+def _ends_equal_the_whole(x, st, p, filt, axis, n, **kw):
+    """A call's first and last n rows (axis 0) or columns (1) equal the same
+    calls on those alone; the blur and the median reach 8 at most."""
+    halo, size = 8, x.shape[1 + axis]
+    part = lambda t, lo, hi, a: t.narrow(a, lo, hi - lo)
+    ends = []
+    for lo, hi, keep in ((0, n + halo, 0), (size - n - halo, size, halo)):
+        s = dsgm.State(*(part(t, lo, hi, axis).clone() for t in st.planes()))
+        out = dsgm.forward_filtered(part(x, lo, hi, 1 + axis).contiguous(), s, p, filt, filtered=True, **kw)
+        ends.append((lo, hi, keep, s, out))
+    out = dsgm.forward_filtered(x, st, p, filt, filtered=True, **kw)
+    for lo, hi, keep, s, o in ends:
+        cut = lambda t, a: part(t, keep, keep + n, a)
+        for k in out:
+            assert torch.equal(cut(part(out[k], lo, hi, 1 + axis), 1 + axis), cut(o[k], 1 + axis)), k
+        for a, b in zip(st.planes(), s.planes()):
+            assert torch.equal(cut(part(a, lo, hi, axis), axis), cut(b, axis))
+
+
+@pytest.mark.parametrize("u8,codes,H", [(True, False, (1 << 27) + 8), (True, True, (1 << 28) + 16),
+                                        (False, False, (1 << 28) + 16)])
+def test_frames_of_more_tiles_than_a_grid_dimension(u8, codes, H):
+    """One column of so many rows that the tiles of 8 (16) rows and 256 lanes are
+    2^32 lanes and more, which a grid's x takes modulo 2^32."""
+    x, st, p = _random(H, 1, 2, u8, 5)
+    _ends_equal_the_whole(x, st, p, dsgm.gauss_filter(3, 1.0, True), 0, 1000, codes=codes)
