@@ -765,7 +765,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
     const int i = tid + l * NT < E::CELLS ? tid + l * NT : 0;
     const int r = i / E::DW, c = i - r * E::DW;
     roff[l] = uint32_t(geom::clamp64(y0 - G::R + r, a.H - 1) * a.row_stride);  // < 2^31 (host check)
-    xb[l] = int32_t(x0) - G::R + 4 * c;
+    xb[l] = int32_t(geom::min64(x0 - G::R + 4 * c, a.W - 1));  // (later columns clamp to it)
     slot[l] = uint32_t(r * E::RP + c);
   }
   // the median's rows and columns in the blurred tile, clamped to the frame
@@ -820,7 +820,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
         nxt[l] = 0;
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          const int64_t xx = geom::clamp64(xb[l] + b, a.W - 1);
+          const int64_t xx = geom::clamp64(int64_t(xb[l]) + b, a.W - 1);
           nxt[l] |= uint32_t(f[roff[l] + xx]) << (8 * b);
         }
       }

@@ -47,3 +47,10 @@ def test_frames_of_more_tiles_than_a_grid_dimension(u8, codes, H):
     2^32 lanes and more, which a grid's x takes modulo 2^32."""
     x, st, p = _random(H, 1, 2, u8, 5)
     _ends_equal_the_whole(x, st, p, dsgm.gauss_filter(3, 1.0, True), 0, 1000, codes=codes)
+
+
+def test_u8_widest_frame():
+    """One row of 2^31 - 1 columns, the widest frame: the columns past the last
+    one that the last tile stages lie beyond 2^31."""
+    x, st, p = _random(1, (1 << 31) - 1, 2, True, 6)
+    _ends_equal_the_whole(x, st, p, dsgm.gauss_filter(5, 1.0, True), 1, 1000)
