@@ -289,8 +289,8 @@ __device__ __forceinline__ double update_in_place(Model<double>& s, const double
       "s_andn2_b64 exec, %[all], %[h]\n\t"
       "v_add_f64 %[vC], %[vC], %[t]\n\t"
       "s_mov_b64 exec, %[all]"
-      : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [mC] "+v"(s.mC), [vC] "+v"(s.vC), [aA] "+v"(s.aA),
-        [aC] "+v"(s.aC), [q] "+v"(qa), [d] "=&v"(d), [t] "=&v"(t), [all] "=&s"(all)
+      : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [mC] "+&v"(s.mC), [vC] "+&v"(s.vC), [aA] "+&v"(s.aA),
+        [aC] "+&v"(s.aC), [q] "+&v"(qa), [d] "=&v"(d), [t] "=&v"(t), [all] "=&s"(all)
       : [x] "v"(x), [u] "v"(e.u), [w] "v"(e.w), [r] "v"(e.r), [n] "v"(e.next), [h] "s"(hit_a),
         [qd] "n"(QD ? 1 : 0)
       : "scc");
@@ -323,8 +323,8 @@ __device__ __forceinline__ float update_in_place(Model<float>& s, const float x,
       "s_andn2_b64 exec, %[all], %[h]\n\t"
       "v_fma_f32 %[vC], %[u], %[vC], %[t]\n\t"
       "s_mov_b64 exec, %[all]"
-      : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [mC] "+v"(s.mC), [vC] "+v"(s.vC), [aA] "+v"(s.aA),
-        [aC] "+v"(s.aC), [q] "+v"(qa), [d] "=&v"(d), [t] "=&v"(t), [all] "=&s"(all)
+      : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [mC] "+&v"(s.mC), [vC] "+&v"(s.vC), [aA] "+&v"(s.aA),
+        [aC] "+&v"(s.aC), [q] "+&v"(qa), [d] "=&v"(d), [t] "=&v"(t), [all] "=&s"(all)
       : [x] "v"(x), [u] "v"(e.u), [w] "v"(e.w), [r] "v"(e.r), [n] "v"(e.next), [h] "s"(hit_a),
         [qd] "n"(QD ? 1 : 0)
       : "scc");
@@ -344,7 +344,7 @@ __device__ __forceinline__ int slot_of(const Model<Acc>& s, const uint64_t hit_a
       "s_mov_b64 exec, %[h]\n\t"
       "v_mov_b32 %[i], %[aA]\n\t"
       "s_mov_b64 exec, %[all]"
-      : [i] "+v"(idx), [all] "=&s"(all)
+      : [i] "+&v"(idx), [all] "=&s"(all)
       : [aA] "v"(s.aA), [h] "s"(hit_a));
   return idx;
 }
@@ -445,8 +445,8 @@ __device__ __forceinline__ void swap_in_place(Model<double>& s, const double x,
       "v_mul_f64 %[q], %[q], %[q]\n\t"
       ".endif\n\t"
       "s_mov_b64 exec, %[all]"
-      : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [mC] "+v"(s.mC), [vC] "+v"(s.vC), [aA] "+v"(s.aA),
-        [aC] "+v"(s.aC), [q] "+v"(qd), [all] "=&s"(all)
+      : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [mC] "+&v"(s.mC), [vC] "+&v"(s.vC), [aA] "+&v"(s.aA),
+        [aC] "+&v"(s.aC), [q] "+&v"(qd), [all] "=&s"(all)
       : [x] "v"(x), [vi] "v"(k.var_init), [h] "s"(swap),
         [one] "n"(int(sizeof(TableEntry<double>))), [qdf] "n"(QD ? 1 : 0));
 }
@@ -468,8 +468,8 @@ __device__ __forceinline__ void swap_in_place(Model<float>& s, const float x,
       "v_mul_f32 %[q], %[q], %[q]\n\t"
       ".endif\n\t"
       "s_mov_b64 exec, %[all]"
-      : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [mC] "+v"(s.mC), [vC] "+v"(s.vC), [aA] "+v"(s.aA),
-        [aC] "+v"(s.aC), [q] "+v"(qd), [all] "=&s"(all)
+      : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [mC] "+&v"(s.mC), [vC] "+&v"(s.vC), [aA] "+&v"(s.aA),
+        [aC] "+&v"(s.aC), [q] "+&v"(qd), [all] "=&s"(all)
       : [x] "v"(x), [vi] "v"(k.var_init), [h] "s"(swap),
         [one] "n"(int(sizeof(TableEntry<float>))), [qdf] "n"(QD ? 1 : 0));
 }

@@ -96,7 +96,7 @@ __device__ __forceinline__ Record8 step8(Model8& s, const uint32_t x, const uint
       "v_mov_b32 %[m], %[mA]\n\t"
       "v_mov_b32 %[v], %[vA]\n\t"
       "s_mov_b64 exec, %[all]"
-      : [i] "+v"(idx), [m] "+v"(m), [v] "+v"(v), [all] "=&s"(all)
+      : [i] "+&v"(idx), [m] "+&v"(m), [v] "+&v"(v), [all] "=&s"(all)
       : [aA] "v"(s.aA), [mA] "v"(s.mA), [vA] "v"(s.vA), [h] "s"(r.hit_a));
   const TableEntry<double>& e = *reinterpret_cast<const TableEntry<double>*>(
       reinterpret_cast<const char*>(t.e) + idx);
@@ -122,8 +122,8 @@ __device__ __forceinline__ Record8 step8(Model8& s, const uint32_t x, const uint
         "v_mov_b32 %[tC], %[t]\n\t"
         "v_mov_b32 %[aC], %[n]\n\t"
         "s_mov_b64 exec, %[all]"
-        : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [tA] "+v"(s.tA), [aA] "+v"(s.aA), [mC] "+v"(s.mC),
-          [vC] "+v"(s.vC), [tC] "+v"(s.tC), [aC] "+v"(s.aC), [all] "=&s"(all)
+        : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [tA] "+&v"(s.tA), [aA] "+&v"(s.aA), [mC] "+&v"(s.mC),
+          [vC] "+&v"(s.vC), [tC] "+&v"(s.tC), [aC] "+&v"(s.aC), [all] "=&s"(all)
         : [m] "v"(mi), [v] "v"(vi), [t] "v"(tn), [n] "v"(next), [h] "s"(r.hit_a)
         : "scc");
   } else {
@@ -137,8 +137,8 @@ __device__ __forceinline__ Record8 step8(Model8& s, const uint32_t x, const uint
         "v_mov_b32 %[vC], %[v]\n\t"
         "v_mov_b32 %[aC], %[n]\n\t"
         "s_mov_b64 exec, %[all]"
-        : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [aA] "+v"(s.aA), [mC] "+v"(s.mC), [vC] "+v"(s.vC),
-          [aC] "+v"(s.aC), [all] "=&s"(all)
+        : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [aA] "+&v"(s.aA), [mC] "+&v"(s.mC), [vC] "+&v"(s.vC),
+          [aC] "+&v"(s.aC), [all] "=&s"(all)
         : [m] "v"(mi), [v] "v"(vi), [n] "v"(next), [h] "s"(r.hit_a)
         : "scc");
   }
@@ -164,8 +164,8 @@ __device__ __forceinline__ void exchange8(Model8& s, const uint32_t x, const uin
       "v_mov_b32 %[tC], %[t]\n\t"
       "v_mov_b32 %[aC], %[one]\n\t"
       "s_mov_b64 exec, %[all]"
-      : [mA] "+v"(s.mA), [vA] "+v"(s.vA), [tA] "+v"(s.tA), [aA] "+v"(s.aA), [mC] "+v"(s.mC),
-        [vC] "+v"(s.vC), [tC] "+v"(s.tC), [aC] "+v"(s.aC), [all] "=&s"(all)
+      : [mA] "+&v"(s.mA), [vA] "+&v"(s.vA), [tA] "+&v"(s.tA), [aA] "+&v"(s.aA), [mC] "+&v"(s.mC),
+        [vC] "+&v"(s.vC), [tC] "+&v"(s.tC), [aC] "+&v"(s.aC), [all] "=&s"(all)
       : [x] "v"(x), [v] "v"(var_init), [t] "v"(ti), [h] "s"(swap),
         [one] "n"(int(sizeof(TableEntry<double>))));
 }
