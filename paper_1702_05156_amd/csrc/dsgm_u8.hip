@@ -605,7 +605,21 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 // and the bound on the rounding of every product and addition, blur_fits()), so
 // its integer part is known too unless an integer lies that near the sum; those
 // cells (about one in 3,000 on noisy frames) are evaluated in single precision, in
-// the appendix's order.
+// the appendix's order, one by one while their wavefront waits.
+//
+// Without noise many sums are integers (a ramp of one level a pixel: 99 % of the
+// cells are undecided; a flat area: all).  A workgroup that finds DENSE8 lanes or
+// more with undecided cells therefore forms all its sums in single precision, four
+// adjacent cells a lane, until a later look (every eighth frame) finds fewer; its
+// first frame it forms so too.  The way does not change a byte.  50 x 1080 x 1920
+// on MI355X, 3 / 5 / 7 taps: ramp 577 / 768 / 1,784 us with every undecided cell
+// by itself, 317 / 440 / 622 us so; pre_u8_kernel below 401 / 477 / 689 us; flat
+// frames 439 and 620 us (5, 7 taps); noise 309 / 333 / 491 and 291 / 337 / 468 us.
+// Limits of 2, 4, 12 and 32 lanes: noise with flat squares on 5 % of the frame
+// 422 / 419 / 419 / 412 us, on 30 % 479 / 484 / 499 / 534 us, a smooth pattern
+// (4 % undecided) 441 / 441 / 491 / 606 us.  Slowest against
+// pre_u8_kernel is what a look can't foretell: flat squares on 30 % of the frame, at
+// other places in every frame (486 / 478 us; 7 taps 806 / 688 us).
 //
 // One matrix product covers 16 windows of 16 bytes in four rows: column n of B
 // is a window (lane n % 16 holds 16 bytes of row lane / 16), row m of A the
@@ -622,10 +636,9 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 // 100 x 480 x 640 (300) 175 / 210 us, 50 x 1080 x 1920 (2,040) 365 / 465 us.
 // Bound by vector issue (about 90 instructions a pixel, half of them the 8-bit
 // update).  pre_u8_kernel, which sums the windows in single precision, took
-// 1,182, 253, 300 and 507 us; 50 x 1920 x 2560: 1,091 against 801 us, and where
-// all windows are flat (every sum undecided, a table gives the byte) 482 against
-// 404 us for 50 x 1080 x 1920.
+// 1,182, 253, 300 and 507 us.
 constexpr int64_t SMALL8_BELOW = 256;
+constexpr uint32_t DENSE8 = 4;
 
 typedef int32_t V4 __attribute__((ext_vector_type(4)));
 
@@ -643,6 +656,8 @@ struct Geo8 {
   static constexpr int WIN = G::GB_H * CG;                 // windows of a tile
   static constexpr int GROUPS = (WIN + 15) / 16;
   static constexpr int SETS = N > 4 ? 2 : 1;               // products per group and digit
+  static constexpr int QR = (G::GB_W + 3) / 4;             // four-cell groups of a blurred row
+  static constexpr int QUADS = G::GB_H * QR;
   static_assert(4 * SETS > N, "a row of zeros");
   static_assert(OW + N - 1 <= 16 && OW % 4 == 0, "a window's outputs read its 16 bytes");
 };
@@ -681,7 +696,8 @@ __device__ __forceinline__ int32_t fixed24(float w) {
 
 template <int RG, bool MED, bool PRINTED, typename Tile>
 __global__ void __launch_bounds__(geom::pre::NT)
-    __attribute__((amdgpu_waves_per_eu(4))) pre_u8_mfma_kernel(const PreArgs a) {
+    __attribute__((amdgpu_waves_per_eu(RG == 1 ? 5 : 4)))  // 3 taps, noise: 291 us at 5, 330 at 4
+    pre_u8_mfma_kernel(const PreArgs a) {
   using E = Geo8<RG, MED, Tile>;
   using G = typename E::G;
   constexpr int N = E::N, PX = G::PX, TH = G::TH, TW = G::TW, NT = geom::pre::NT;
@@ -692,7 +708,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
   // the weights' digits as bytes, a window row at byte 16 of a row of zeros
   __shared__ uint32_t digits[3][4 * E::SETS][9];
   __shared__ int32_t centre128;  // 128 times the sum of the fixed-point weights
-  __shared__ uint32_t flat[256];  // the blurred byte of a window of one level
+  __shared__ uint32_t undecided[NT / 64];  // lanes with undecided cells, by wavefront
   const int64_t tile = tile_here(a);
   if (tile < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -700,6 +716,8 @@ __global__ void __launch_bounds__(geom::pre::NT)
   const StepConsts<double> k =
       make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
   for (int i = tid; i < int(sizeof(digits) / 4); i += NT) (&digits[0][0][0])[i] = 0u;
+  // (columns past the staged ones: cells that no lane takes, but sums that count)
+  for (int i = tid; i < G::RAW_H * E::RP; i += NT) raw[i] = 0x80808080u;
   if (tid == 0) centre128 = 0;
   __syncthreads();
   for (int e = tid; e < N * N; e += NT) {
@@ -741,15 +759,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
 #pragma unroll
   for (int e = 0; e < N * N; ++e)
     w2[e] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wf[e])));
-  for (int c = tid; c < 256; c += NT) {  // (read after the frame loop's first barrier)
-    float blur = 0.0f;
-#pragma unroll
-    for (int e = 0; e < N * N; ++e) {
-      const float prod = float(c) * w2[e];
-      blur = blur + prod;
-    }
-    flat[c] = uint32_t(__builtin_fminf(255.0f, blur));
-  }
+  const float near = float(a.blur_width) * 0x1p-24f;
 
   const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
   const int ty = G::lane_row(tid), tx = G::lane_col(tid);
@@ -758,14 +768,15 @@ __global__ void __launch_bounds__(geom::pre::NT)
   // this lane's staged dwords: frame row offset, first column, LDS index.  Where
   // no column of the tile leaves the frame a dword is one (unaligned) load.
   const bool inner = x0 >= G::R && x0 - G::R + 4 * E::DW <= a.W;
-  uint32_t roff[E::LD], slot[E::LD];
-  int32_t xb[E::LD];
+  uint32_t off[E::LD][4], slot[E::LD];  // the four bytes' frame offsets (< 2^31, host check)
 #pragma unroll
   for (int l = 0; l < E::LD; ++l) {
     const int i = tid + l * NT < E::CELLS ? tid + l * NT : 0;
     const int r = i / E::DW, c = i - r * E::DW;
-    roff[l] = uint32_t(geom::clamp64(y0 - G::R + r, a.H - 1) * a.row_stride);  // < 2^31 (host check)
-    xb[l] = int32_t(geom::min64(x0 - G::R + 4 * c, a.W - 1));  // (later columns clamp to it)
+    const int64_t row = geom::clamp64(y0 - G::R + r, a.H - 1) * a.row_stride;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      off[l][b] = uint32_t(row + geom::clamp64(x0 - G::R + 4 * c + b, a.W - 1));
     slot[l] = uint32_t(r * E::RP + c);
   }
   // the median's rows and columns in the blurred tile, clamped to the frame
@@ -812,22 +823,19 @@ __global__ void __launch_bounds__(geom::pre::NT)
     typedef uint32_t U1 __attribute__((aligned(1)));
     if (inner) {
 #pragma unroll
-      for (int l = 0; l < E::LD; ++l)
-        nxt[l] = *reinterpret_cast<const U1*>(f + roff[l] + uint32_t(xb[l]));
+      for (int l = 0; l < E::LD; ++l) nxt[l] = *reinterpret_cast<const U1*>(f + off[l][0]);
     } else {
 #pragma unroll
       for (int l = 0; l < E::LD; ++l) {
         nxt[l] = 0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int64_t xx = geom::clamp64(int64_t(xb[l]) + b, a.W - 1);
-          nxt[l] |= uint32_t(f[roff[l] + xx]) << (8 * b);
-        }
+        for (int b = 0; b < 4; ++b) nxt[l] |= uint32_t(f[off[l][b]]) << (8 * b);
       }
     }
   };
   if (a.T > 0) load_frame(0);
 
+  bool plain = true;
   for (int64_t t = 0; t < a.T; ++t) {
     // 1. stage the raw bytes, then start loading the next frame's
 #pragma unroll
@@ -837,92 +845,118 @@ __global__ void __launch_bounds__(geom::pre::NT)
     if (t + 1 < a.T) load_frame(t + 1);
 
     // 2. the blurred bytes of the tile and the median's halo
-    for (int grp = wave; grp < E::GROUPS; grp += NT / 64) {
-      const int win = grp * 16 + m, wr = win < E::WIN ? win / E::CG : 0;
-      const int wc = win < E::WIN ? (win - wr * E::CG) * E::OW : 0;
-      V4 acc[3] = {V4{centre, centre, centre, centre}, V4{0, 0, 0, 0}, V4{0, 0, 0, 0}};
+    const bool look = t == 0 || (t & 7) == 7;  // whether this frame decides the next ones' way
+    uint32_t n_undecided = 0;
+    if (plain) {
+      // every sum in the appendix's order, four adjacent cells a lane
+#pragma unroll 1
+      for (int c = tid; c < E::QUADS; c += NT) {
+        const int r = c / E::QR, q0 = c - r * E::QR;
+        const uint32_t* src = raw + r * E::RP + q0;
+        float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int st = 0; st < E::SETS; ++st) {
-        // rows past the window carry zero weights; they read its last row
-        const int dy = 4 * st + rgrp < N ? 4 * st + rgrp : N - 1;
-        const uint32_t* src = raw + (wr + dy) * E::RP + wc / 4;
-        const V4 B = {int32_t(src[0]), int32_t(src[1]), int32_t(src[2]), int32_t(src[3])};
+        for (int y = 0; y < N; ++y) {
+          float v[N + 3];
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-          acc[q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[st][q], B, acc[q], 0, 0, 0);
-      }
-      // this lane has outputs 4*rgrp .. + 3 of its window
-      uint32_t out[4], frac[4];
+          for (int x = 0; x < N + 3; ++x)
+            v[x] = float(((src[y * E::RP + x / 4] ^ 0x80808080u) >> (8 * (x & 3))) & 0xFFu);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t sum =
-            (((uint32_t(acc[2][i]) << 8) + uint32_t(acc[1][i])) << 8) + uint32_t(acc[0][i]);
-        out[i] = sum >> 24;
-        frac[i] = sum << 8;
-      }
-      const bool mine = win < E::WIN && 4 * rgrp < E::OW && wc + 4 * rgrp < G::GB_W;
-      const uint32_t low = frac[0] < frac[1] ? frac[0] : frac[1];
-      if (__builtin_amdgcn_ballot_w64(mine && min3u(low, frac[2], frac[3]) < width8) != 0) {
-        // an integer (not zero: the sum is not negative) lies too near one of the
-        // sums: each lane evaluates its undecided cells one by one
-        uint32_t todo = 0;
+          for (int x = 0; x < N; ++x)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          todo |= mine && frac[i] < width8 && out[i] != 0 ? 1u << i : 0u;
-        // saturated and other flat areas are undecided everywhere: where the
-        // four windows hold one level the byte is the table's
-        const uint32_t* own = raw + wr * E::RP + wc / 4 + (mine ? rgrp : 0);
-        const uint32_t level = own[0] & 0xFFu, all4 = level * 0x01010101u;
-        uint32_t diff = 0;
-#pragma unroll
-        for (int y = 0; y < N; ++y)
-#pragma unroll
-          for (int q = 0; q < (N + 6) / 4; ++q) {
-            const uint32_t d = own[y * E::RP + q] ^ all4;
-            diff |= 4 * q + 4 <= N + 3 ? d : d & 0xFFFFu;  // N + 3 columns, an even number
-          }
-        if (todo != 0 && diff == 0) {
-          const uint32_t v = flat[level ^ 0x80u];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) out[q] = v;
-          todo = 0;
-        }
-        while (__builtin_amdgcn_ballot_w64(todo != 0) != 0) {
-          const int i = todo != 0 ? __builtin_ctz(todo) : 0;
-          // (a lane that is done reads its window's first columns)
-          const int col = todo != 0 ? wc + 4 * rgrp + i : wc, sh = col & 3;
-          const uint32_t* src = raw + wr * E::RP + col / 4;
-          // a window row's N bytes lie in at most three dwords
-          uint32_t d[N][3];
-#pragma unroll
-          for (int y = 0; y < N; ++y)
-#pragma unroll
-            for (int q = 0; q < (N > 5 ? 3 : 2); ++q) d[y][q] = src[y * E::RP + q] ^ 0x80808080u;
-          float blur = 0.0f;
-#pragma unroll
-          for (int y = 0; y < N; ++y) {
-            const uint32_t b0 = __builtin_amdgcn_alignbyte(d[y][1], d[y][0], sh);
-            const uint32_t b1 = N > 5 ? __builtin_amdgcn_alignbyte(d[y][2], d[y][1], sh)
-                                      : d[y][1] >> (8 * sh);
-#pragma unroll
-            for (int x = 0; x < N; ++x) {
-              const uint32_t byte = ((x < 4 ? b0 : b1) >> (8 * (x & 3))) & 0xFFu;
-              const float prod = float(byte) * w2[y * N + x];
-              blur = blur + prod;
+            for (int i = 0; i < 4; ++i) {
+              const float prod = v[x + i] * w2[y * N + x];
+              sum[i] = sum[i] + prod;
             }
-          }
-          const uint32_t v = uint32_t(__builtin_fminf(255.0f, blur));
-#pragma unroll
-          for (int q = 0; q < 4; ++q) out[q] = todo != 0 && q == i ? v : out[q];
-          todo &= todo - 1;
         }
+        Vec<uint32_t, 4> out;
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          out.v[i] = uint32_t(__builtin_fminf(255.0f, sum[i]));
+          any |= __builtin_fabsf(sum[i] - __builtin_rintf(sum[i])) < near && sum[i] > 0.5f;
+        }
+        n_undecided += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(any)));
+        *reinterpret_cast<Vec<uint32_t, 4>*>(gb + r * E::GBP + 4 * q0) = out;
       }
-      if (mine) {
-        uint32_t* dst = gb + wr * E::GBP + wc + 4 * rgrp;
-        *reinterpret_cast<Vec<uint32_t, 4>*>(dst) = Vec<uint32_t, 4>{{out[0], out[1], out[2], out[3]}};
+    } else {
+      for (int grp = wave; grp < E::GROUPS; grp += NT / 64) {
+        const int win = grp * 16 + m, wr = win < E::WIN ? win / E::CG : 0;
+        const int wc = win < E::WIN ? (win - wr * E::CG) * E::OW : 0;
+        V4 acc[3] = {V4{centre, centre, centre, centre}, V4{0, 0, 0, 0}, V4{0, 0, 0, 0}};
+#pragma unroll
+        for (int st = 0; st < E::SETS; ++st) {
+          // rows past the window carry zero weights; they read its last row
+          const int dy = 4 * st + rgrp < N ? 4 * st + rgrp : N - 1;
+          const uint32_t* src = raw + (wr + dy) * E::RP + wc / 4;
+          const V4 B = {int32_t(src[0]), int32_t(src[1]), int32_t(src[2]), int32_t(src[3])};
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            acc[q] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[st][q], B, acc[q], 0, 0, 0);
+        }
+        // this lane has outputs 4*rgrp .. + 3 of its window
+        uint32_t out[4], frac[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t sum =
+              (((uint32_t(acc[2][i]) << 8) + uint32_t(acc[1][i])) << 8) + uint32_t(acc[0][i]);
+          out[i] = sum >> 24;
+          frac[i] = sum << 8;
+        }
+        const bool mine = win < E::WIN && 4 * rgrp < E::OW && wc + 4 * rgrp < G::GB_W;
+        const uint32_t low = frac[0] < frac[1] ? frac[0] : frac[1];
+        if (__builtin_amdgcn_ballot_w64(mine && min3u(low, frac[2], frac[3]) < width8) != 0) {
+          // an integer (not zero: the sum is not negative) lies too near one of the
+          // sums: the undecided cells are evaluated in the appendix's order
+          uint32_t todo = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            todo |= mine && frac[i] < width8 && out[i] != 0 ? 1u << i : 0u;
+          if (look)
+            n_undecided += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(todo != 0)));
+          while (__builtin_amdgcn_ballot_w64(todo != 0) != 0) {
+            const int i = todo != 0 ? __builtin_ctz(todo) : 0;
+            // (a lane that is done reads its window's first columns)
+            const int col = todo != 0 ? wc + 4 * rgrp + i : wc, sh = col & 3;
+            const uint32_t* src = raw + wr * E::RP + col / 4;
+            // a window row's N bytes lie in at most three dwords
+            uint32_t d[N][3];
+#pragma unroll
+            for (int y = 0; y < N; ++y)
+#pragma unroll
+              for (int q = 0; q < (N > 5 ? 3 : 2); ++q) d[y][q] = src[y * E::RP + q] ^ 0x80808080u;
+            float blur = 0.0f;
+#pragma unroll
+            for (int y = 0; y < N; ++y) {
+              const uint32_t b0 = __builtin_amdgcn_alignbyte(d[y][1], d[y][0], sh);
+              const uint32_t b1 = N > 5 ? __builtin_amdgcn_alignbyte(d[y][2], d[y][1], sh)
+                                        : d[y][1] >> (8 * sh);
+#pragma unroll
+              for (int x = 0; x < N; ++x) {
+                const uint32_t byte = ((x < 4 ? b0 : b1) >> (8 * (x & 3))) & 0xFFu;
+                const float prod = float(byte) * w2[y * N + x];
+                blur = blur + prod;
+              }
+            }
+            const uint32_t v = uint32_t(__builtin_fminf(255.0f, blur));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out[q] = todo != 0 && q == i ? v : out[q];
+            todo &= todo - 1;
+          }
+        }
+        if (mine) {
+          uint32_t* dst = gb + wr * E::GBP + wc + 4 * rgrp;
+          *reinterpret_cast<Vec<uint32_t, 4>*>(dst) = Vec<uint32_t, 4>{{out[0], out[1], out[2], out[3]}};
+        }
       }
     }
+    if (look) {  // (uniform, as the test of the lane is not)
+      if (lane == 0) undecided[wave] = n_undecided;
+    }
     __syncthreads();
+    if (look) {
+      const uint32_t n = undecided[0] + undecided[1] + undecided[2] + undecided[3];
+      plain = __builtin_amdgcn_readfirstlane(n) >= DENSE8;
+    }
 
     // 3. each pixel's median of the nine blurred bytes, then the 8-bit update
     uint32_t xs[PX];
