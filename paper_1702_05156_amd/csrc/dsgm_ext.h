@@ -31,9 +31,6 @@ struct PreArgs {
   double theta_s, theta_d, var_init, var_floor, mask_floor;
   int32_t age_max, weight_rule, mask_rule;
   double w[7];  // blur weights, 2*rg+1 of them
-  // 8-bit form, in units of 2^-24: the single-precision blur sum lies at most
-  // blur_above above the fixed-point one and blur_width - blur_above below it
-  uint32_t blur_above, blur_width;
 };
 
 // rg: blur radius 0..3 (0: no blur); median: 3 x 3 median after the blur

@@ -602,7 +602,7 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 // rounded to multiples of 2^-24, split into three signed bytes, and the window
 // sums are products of 8-bit matrices with 32-bit sums.  How far the
 // single-precision result can lie from that sum is known (the weights' rounding
-// and the bound on the rounding of every product and addition, blur_fits()), so
+// and the bound on the rounding of every product and addition, blur_weights()), so
 // its integer part is known too unless an integer lies that near the sum; those
 // cells (about one in 3,000 on noisy frames) are evaluated in single precision, in
 // the appendix's order, one by one while their wavefront waits.
@@ -678,89 +678,33 @@ __device__ __forceinline__ uint32_t max3u(uint32_t a, uint32_t b, uint32_t c) {
   return r;
 }
 
-// the window weight float(w_i * w_j) of entry e = i*N + j, and its fixed point
-template <int N>
-__device__ __forceinline__ float window_weight(const double* w, int e) {
-  const int i = e / N, j = e - i * N;
-  double wi = w[0], wj = w[0];
-#pragma unroll
-  for (int q = 1; q < N; ++q) {
-    wi = i == q ? w[q] : wi;
-    wj = j == q ? w[q] : wj;
-  }
-  return float(wi * wj);
-}
-__device__ __forceinline__ int32_t fixed24(float w) {
-  return int32_t(__builtin_rint(double(w) * 16777216.0));
-}
+// A call's window weights, prepared on the host (blur_weights()): row-major, the
+// sums' bound in units of 2^-24 (the single-precision sum lies at most `above`
+// above the fixed-point one and width - above below it; 0: the weights don't fit),
+// 128 times the fixed-point weights' sum, and the fixed-point weights' three
+// signed bytes, each window row from byte 16 of a row of zeros.
+struct Blur8 {
+  float w[49];
+  uint32_t above, width, centre128;
+  uint32_t digits[3][8][9];
+};
 
 template <int RG, bool MED, bool PRINTED, typename Tile>
 __global__ void __launch_bounds__(geom::pre::NT)
     __attribute__((amdgpu_waves_per_eu(RG == 1 ? 5 : 4)))  // 3 taps, noise: 291 us at 5, 330 at 4
-    pre_u8_mfma_kernel(const PreArgs a) {
+    pre_u8_mfma_kernel(const PreArgs a, const Blur8 f) {
   using E = Geo8<RG, MED, Tile>;
   using G = typename E::G;
   constexpr int N = E::N, PX = G::PX, TH = G::TH, TW = G::TW, NT = geom::pre::NT;
   __shared__ alignas(16) uint32_t raw[G::RAW_H * E::RP];   // bytes with the top bit flipped
   __shared__ alignas(16) uint32_t gb[G::GB_H * E::GBP];    // blurred bytes, one to a dword
   __shared__ Tables8 tbl;
-  __shared__ float wf[N * N];
-  // the weights' digits as bytes, a window row at byte 16 of a row of zeros
-  __shared__ uint32_t digits[3][4 * E::SETS][9];
-  __shared__ int32_t centre128;  // 128 times the sum of the fixed-point weights
   __shared__ uint32_t undecided[NT / 64];  // lanes with undecided cells, by wavefront
   const int64_t tile = tile_here(a);
   if (tile < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const StepConsts<double> k =
-      make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
-  for (int i = tid; i < int(sizeof(digits) / 4); i += NT) (&digits[0][0][0])[i] = 0u;
-  // (columns past the staged ones: cells that no lane takes, but sums that count)
-  for (int i = tid; i < G::RAW_H * E::RP; i += NT) raw[i] = 0x80808080u;
-  if (tid == 0) centre128 = 0;
-  __syncthreads();
-  for (int e = tid; e < N * N; e += NT) {
-    const float w = window_weight<N>(a.w, e);
-    const int32_t W = fixed24(w);
-    const int32_t d0 = int8_t(W), W1 = (W - d0) >> 8, d1 = int8_t(W1), d2 = (W1 - d1) >> 8;
-    const int32_t d[3] = {d0, d1, d2};
-    wf[e] = w;
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      reinterpret_cast<int8_t*>(digits[q][e / N])[16 + e % N] = int8_t(d[q]);
-    atomicAdd(&centre128, 128 * W);
-  }
-  fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
-  const uint32_t var_init = uint32_t(a.var_init);
-
-  // A: output m = lane % 16, row group lane / 16, byte j: the weight's digit of
-  // window row dy, window column j - m (formed once a weight and read shifted:
-  // every lane converting its own 32 bytes cost as much as the frames of a short
-  // call)
-  const int m = lane & 15, rgrp = lane >> 4;
-  V4 A[E::SETS][3];
-#pragma unroll
-  for (int st = 0; st < E::SETS; ++st)
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      // bytes 16 - m .. 31 - m of the row (row N is zero, for lanes without an output)
-      const uint32_t* row = digits[q][m < E::OW ? 4 * st + rgrp : N] + (16 - m) / 4;
-#pragma unroll
-      for (int dw = 0; dw < 4; ++dw)
-        A[st][q][dw] = int32_t(__builtin_amdgcn_alignbyte(row[dw + 1], row[dw], uint32_t(-m) & 3u));
-    }
-  // the bytes are staged less 128: the sum gets 128 times the weights back
-  // and the sum's upper end is what is formed: its integer part is the result's
-  // unless the integer lies less than blur_width below it
-  const int32_t centre = int32_t(a.blur_above) + centre128;
-  const uint32_t width8 = a.blur_width << 8;  // compared with the fraction in the top 24 bits
-  float w2[N * N];  // the window's weights in scalar registers
-#pragma unroll
-  for (int e = 0; e < N * N; ++e)
-    w2[e] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wf[e])));
-  const float near = float(a.blur_width) * 0x1p-24f;
-
+  const bool fixed = f.width != 0;  // the weights fit the fixed point
   const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
   const int ty = G::lane_row(tid), tx = G::lane_col(tid);
   const int64_t gy = y0 + ty;
@@ -801,39 +745,65 @@ __global__ void __launch_bounds__(geom::pre::NT)
 
   uint8_t* const planes[4] = {static_cast<uint8_t*>(a.mean_a), static_cast<uint8_t*>(a.var_a),
                               static_cast<uint8_t*>(a.mean_c), static_cast<uint8_t*>(a.var_c)};
-  Model8 s[PX];
-  {
-    Planes8<PX> b;
+  // the state and the first frame are requested before the tables are built
+  Planes8<PX> first;
 #pragma unroll
-    for (int q = 0; q < PX; ++q) {
-      b.mA.v[q] = valid[q] ? planes[0][pix + q] : uint8_t(0);
-      b.vA.v[q] = valid[q] ? planes[1][pix + q] : uint8_t(0);
-      b.mC.v[q] = valid[q] ? planes[2][pix + q] : uint8_t(0);
-      b.vC.v[q] = valid[q] ? planes[3][pix + q] : uint8_t(0);
-      b.aA.v[q] = valid[q] ? a.age_a[pix + q] : uint8_t(1);
-      b.aC.v[q] = valid[q] ? a.age_c[pix + q] : uint8_t(1);
-    }
-    unpack8<PX>(b, tbl, s);
+  for (int q = 0; q < PX; ++q) {
+    first.mA.v[q] = valid[q] ? planes[0][pix + q] : uint8_t(0);
+    first.vA.v[q] = valid[q] ? planes[1][pix + q] : uint8_t(0);
+    first.mC.v[q] = valid[q] ? planes[2][pix + q] : uint8_t(0);
+    first.vC.v[q] = valid[q] ? planes[3][pix + q] : uint8_t(0);
+    first.aA.v[q] = valid[q] ? a.age_a[pix + q] : uint8_t(1);
+    first.aC.v[q] = valid[q] ? a.age_c[pix + q] : uint8_t(1);
   }
 
   const uint8_t* frames = static_cast<const uint8_t*>(a.frames);
   uint32_t nxt[E::LD];
   auto load_frame = [&](int64_t t) {
-    const uint8_t* f = frames + t * a.frame_stride;
+    const uint8_t* x = frames + t * a.frame_stride;
     typedef uint32_t U1 __attribute__((aligned(1)));
     if (inner) {
 #pragma unroll
-      for (int l = 0; l < E::LD; ++l) nxt[l] = *reinterpret_cast<const U1*>(f + off[l][0]);
+      for (int l = 0; l < E::LD; ++l) nxt[l] = *reinterpret_cast<const U1*>(x + off[l][0]);
     } else {
 #pragma unroll
       for (int l = 0; l < E::LD; ++l) {
         nxt[l] = 0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) nxt[l] |= uint32_t(f[off[l][b]]) << (8 * b);
+        for (int b = 0; b < 4; ++b) nxt[l] |= uint32_t(x[off[l][b]]) << (8 * b);
       }
     }
   };
   if (a.T > 0) load_frame(0);
+
+  // A: output m = lane % 16, row group lane / 16, byte j: the weight's digit of
+  // window row dy, window column j - m: bytes 16 - m .. 31 - m of the row (row N
+  // is zero, for lanes without an output)
+  const int m = lane & 15, rgrp = lane >> 4;
+  V4 A[E::SETS][3];
+#pragma unroll
+  for (int st = 0; st < E::SETS; ++st)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t* row = f.digits[q][m < E::OW ? 4 * st + rgrp : N] + (16 - m) / 4;
+#pragma unroll
+      for (int dw = 0; dw < 4; ++dw)
+        A[st][q][dw] = int32_t(__builtin_amdgcn_alignbyte(row[dw + 1], row[dw], uint32_t(-m) & 3u));
+    }
+  // (columns past the staged ones: cells that no lane takes, but sums that count)
+  for (int i = tid; i < G::RAW_H * E::RP; i += NT) raw[i] = 0x80808080u;
+  const StepConsts<double> k =
+      make_consts<double>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
+  fill_tables(tbl, k, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
+  const uint32_t var_init = uint32_t(a.var_init);
+  // the bytes are staged less 128: the sum gets 128 times the weights back
+  // and the sum's upper end is what is formed: its integer part is the result's
+  // unless the integer lies less than `width` below it
+  const int32_t centre = int32_t(f.above + f.centre128);
+  const uint32_t width8 = f.width << 8;  // compared with the fraction in the top 24 bits
+  const float near = float(f.width) * 0x1p-24f;
+  Model8 s[PX];
+  unpack8<PX>(first, tbl, s);
 
   bool plain = true;
   for (int64_t t = 0; t < a.T; ++t) {
@@ -845,7 +815,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
     if (t + 1 < a.T) load_frame(t + 1);
 
     // 2. the blurred bytes of the tile and the median's halo
-    const bool look = t == 0 || (t & 7) == 7;  // whether this frame decides the next ones' way
+    const bool look = fixed && (t == 0 || (t & 7) == 7);  // this frame decides the next ones' way
     uint32_t n_undecided = 0;
     if (plain) {
       // every sum in the appendix's order, four adjacent cells a lane
@@ -864,7 +834,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
           for (int x = 0; x < N; ++x)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              const float prod = v[x + i] * w2[y * N + x];
+              const float prod = v[x + i] * f.w[y * N + x];
               sum[i] = sum[i] + prod;
             }
         }
@@ -872,7 +842,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
         bool any = false;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          out.v[i] = uint32_t(__builtin_fminf(255.0f, sum[i]));
+          out.v[i] = uint32_t(__builtin_fminf(255.0f, __builtin_fmaxf(0.0f, sum[i])));
           any |= __builtin_fabsf(sum[i] - __builtin_rintf(sum[i])) < near && sum[i] > 0.5f;
         }
         n_undecided += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(any)));
@@ -933,7 +903,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
 #pragma unroll
               for (int x = 0; x < N; ++x) {
                 const uint32_t byte = ((x < 4 ? b0 : b1) >> (8 * (x & 3))) & 0xFFu;
-                const float prod = float(byte) * w2[y * N + x];
+                const float prod = float(byte) * f.w[y * N + x];
                 blur = blur + prod;
               }
             }
@@ -1026,41 +996,60 @@ __global__ void __launch_bounds__(geom::pre::NT)
 }
 
 // Half an ulp of a single-precision value up to v, in units of 2^-24.
-double half_ulp24(double v) { return std::exp2(std::floor(std::log2(v))); }
+double half_ulp24(double v) {
+  int e;
+  std::frexp(v, &e);  // v in [2^(e-1), 2^e)
+  return std::ldexp(1.0, e - 1);
+}
 
-// Whether the window's weights fit the fixed-point form, and how far (in units
-// of 2^-24) the appendix's single-precision sum can lie above the fixed-point
-// one, and from its lowest to its highest: the weights' rounding at all pixels
-// whose weight was rounded down (up), and half an ulp of every product and of
-// every partial sum, which are largest with all pixels at 255 (the rounding of
+// The window weights float(w_i * w_j), and, if they fit the fixed-point form,
+// their digits and how far the appendix's single-precision sum can lie above the
+// fixed-point one and from its lowest to its highest: the weights' rounding at all
+// pixels whose weight was rounded down (up), and half an ulp of every product and
+// of every partial sum, which are largest with all pixels at 255 (the rounding of
 // a sum grows with it).
-bool blur_fits(const double* w, int n, uint32_t* above, uint32_t* width) {
+Blur8 blur_weights(const double* w, int n) {
+  Blur8 f{};
+  bool fits = true;
   double total = 0.0, down = 0.0, up = 0.0, chain = 0.0;
   for (int i = 0; i < n; ++i)
     for (int j = 0; j < n; ++j) {
-      const double v = double(float(w[i] * w[j]));
-      if (!(v >= 0.0) || v > 0.49) return false;  // three signed bytes of 2^-24
-      const double off = v * 16777216.0 - std::rint(v * 16777216.0);
+      f.w[i * n + j] = float(w[i] * w[j]);
+      const double v = double(f.w[i * n + j]);
+      fits = fits && v >= 0.0 && v <= 0.49;  // three signed bytes of 2^-24
+      if (!fits) continue;
+      const double fixed = std::rint(v * 16777216.0), off = v * 16777216.0 - fixed;
       (off > 0.0 ? down : up) += std::fabs(off);
       total += v;
       if (v > 0.0) chain += half_ulp24(255.001 * v);
       if (total > v) chain += half_ulp24(255.001 * total);  // the first sum is the product itself
+      int32_t rest = int32_t(fixed);
+      f.centre128 += 128u * uint32_t(rest);
+      for (int q = 0; q < 3; ++q) {
+        const int8_t d = int8_t(rest);  // the low byte, signed
+        rest = (rest - d) / 256;
+        reinterpret_cast<int8_t*>(f.digits[q][i])[16 + j] = d;
+      }
     }
-  if (total > 1.003) return false;  // 255 * total + above stays below 256
-  *above = uint32_t(std::ceil(255.0 * down + 1.0001 * chain)) + 1u;
-  *width = *above + uint32_t(std::ceil(255.0 * up + 1.0001 * chain)) + 1u;
-  return *width < (1u << 20);
+  const double above = std::ceil(255.0 * down + 1.0001 * chain) + 1.0;
+  const double width = above + std::ceil(255.0 * up + 1.0001 * chain) + 1.0;
+  // 255 * total + above stays below 256
+  if (fits && total <= 1.003 && width < double(1u << 20)) {
+    f.above = uint32_t(above);
+    f.width = uint32_t(width);
+  }
+  return f;
 }
 
 template <int RG, bool MED, bool PRINTED>
-hipError_t launch_pre_mfma(PreArgs a, hipStream_t stream) {
+hipError_t launch_pre_mfma(PreArgs a, const Blur8& f, hipStream_t stream) {
   using geom::pre::Small;
   using geom::pre::Wide;
   auto go = [&](auto tile, auto kernel) {
     using Tile = decltype(tile);
     a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
     a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
-    hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a);
+    hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a, f);
     return hipGetLastError();
   };
   if (a.tiles_x * a.tiles_y < SMALL8_BELOW)  // tiles of 16 x 64 (the caller's count)
@@ -1068,26 +1057,41 @@ hipError_t launch_pre_mfma(PreArgs a, hipStream_t stream) {
   return go(Wide{}, pre_u8_mfma_kernel<RG, MED, PRINTED, Wide>);
 }
 
+// The call lengths from which large frames (LARGE8 tiles of 16 x 64 and more) run
+// the matrix kernel; smaller ones always do.  Its set-up and its tiles of half the
+// size have to be paid for by the blur, which without the median's halo and with
+// three taps is too little at any length.  pre_u8_kernel / pre_u8_mfma_kernel on
+// T x 1080 x 1920, us: 5 taps and median T = 1 23.4 / 25.2, 2 32.5 / 32.0, 4 50.1 /
+// 44.0; 7 taps 4 66.8 / 63.3, 6 91.7 / 81.8; 3 taps 2 27.3 / 26.3; without the median 5
+// taps 8 58.8 / 60.4, 32 193.7 / 183.7; 7 taps 2 32.7 / 32.1; 3 taps 32 141.9 / 155.4.
+// On frames without noise (all sums in single precision) 5 taps and median 4 49.7 /
+// 50.8, 7 taps 8 117.8 / 120.9.  480 x 640 (300 tiles): 5 taps and median 1 8.5 / 7.7, 3
+// taps without 32 55.0 / 45.6.
+constexpr int64_t LARGE8 = 512;
+int64_t matrix_from(int rg, bool median) {
+  if (median) return rg == 1 ? 1 : rg == 2 ? 3 : 5;
+  return rg == 1 ? INT64_MAX : rg == 2 ? 16 : 2;
+}
+
 template <bool MED, bool PRINTED>
 hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
   const dim3 grid = tile_grid(a), block{geom::pre::NT, 1, 1};
   // (decision codes, a debug output, exist on pre_u8_kernel only)
-  // A short call on a large frame doesn't pay for the matrix kernel's fragments and
-  // its tiles of half the size.  pre_u8_kernel / pre_u8_mfma_kernel, us, T x 1080
-  // x 1920: 5 taps 26.3 / 29.8 (T = 1), 36.4 / 35.6 (2), 52.6 / 47.7 (4); 3 taps
-  // 23.9 / 25.8, 32.3 / 32.0, 46.1 / 42.0; 7 taps 67.4 / 70.2 (4), 94.2 / 88.6 (6).
-  // 7 taps at 4 x 240 x 320, in 8 x 32 tiles: 18.8 / 14.0.
-  const bool pays = a.T >= (rg < 3 ? 2 : 5) || a.tiles_x * a.tiles_y < SMALL8_BELOW;
-  const bool fits = rg > 0 && pays && !a.codes &&
-                    blur_fits(a.w, 2 * rg + 1, &a.blur_above, &a.blur_width);
-  switch (fits ? rg + 4 : rg) {
+  bool matrix = rg > 0 && !a.codes;
+  Blur8 f;
+  if (matrix) {
+    f = blur_weights(a.w, 2 * rg + 1);
+    matrix = f.width != 0 &&
+             (a.tiles_x * a.tiles_y < LARGE8 || a.T >= matrix_from(rg, MED));
+  }
+  switch (matrix ? rg + 4 : rg) {
     case 0: hipLaunchKernelGGL((pre_u8_kernel<0, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 1: hipLaunchKernelGGL((pre_u8_kernel<1, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 2: hipLaunchKernelGGL((pre_u8_kernel<2, MED, PRINTED>), grid, block, 0, stream, a); break;
     case 3: hipLaunchKernelGGL((pre_u8_kernel<3, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 5: return launch_pre_mfma<1, MED, PRINTED>(a, stream);
-    case 6: return launch_pre_mfma<2, MED, PRINTED>(a, stream);
-    case 7: return launch_pre_mfma<3, MED, PRINTED>(a, stream);
+    case 5: return launch_pre_mfma<1, MED, PRINTED>(a, f, stream);
+    case 6: return launch_pre_mfma<2, MED, PRINTED>(a, f, stream);
+    case 7: return launch_pre_mfma<3, MED, PRINTED>(a, f, stream);
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -77,6 +77,19 @@ def _contents(kind, T, H, W):
     return frames.astype(np.uint8)
 
 
+def _u8_equals_oracle(x, st, p, n, median, sigma=1.0):
+    """The call without decision codes: filtered bytes, masks and state."""
+    host = {k: getattr(st, k).cpu().numpy().ravel() for k in PLANES}
+    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), st, p,
+                                dsgm.gauss_filter(n, sigma, median), filtered=True)
+    xf = oracle.preprocess_u8(x, oracle.gauss_weights(n, sigma), median=bool(median))
+    G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
+    ref = oracle.forward_u8(xf.reshape(len(x), -1), host, G.oracle_params(p))
+    G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.uint8), ref["masks"])
+    for k in PLANES:
+        G.assert_bit_exact(k, getattr(st, k).cpu().numpy().ravel(), ref[k].astype(np.uint8))
+
+
 @pytest.mark.parametrize("kind", ["ramp", "slow ramp", "smooth", "in turn", "half"])
 @pytest.mark.parametrize("H,W", [(37, 150), (190, 1461), (190, 1464)])
 @pytest.mark.parametrize("n,median", [(3, 1), (5, 1), (7, 1), (3, 0), (5, 0), (7, 0)])
@@ -88,12 +101,18 @@ def test_u8_undecided_sums(kind, H, W, n, median):
     x = _contents(kind, T, H, W)
     p = dsgm.dsgm_params_default(255.0, 1)
     st = _random(H, W, 1, True, 7)[1]
-    host = {k: getattr(st, k).cpu().numpy().ravel() for k in PLANES}
-    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), st, p,
-                                dsgm.gauss_filter(n, 1.0, median), filtered=True)
-    xf = oracle.preprocess_u8(x, oracle.gauss_weights(n, 1.0), median=bool(median))
-    G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
-    ref = oracle.forward_u8(xf.reshape(T, -1), host, G.oracle_params(p))
-    G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.uint8), ref["masks"])
-    for k in PLANES:
-        G.assert_bit_exact(k, getattr(st, k).cpu().numpy().ravel(), ref[k].astype(np.uint8))
+    _u8_equals_oracle(x, st, p, n, median)
+
+
+@pytest.mark.parametrize("H,W,n,median,T", [
+    (365, 1461, 3, 1, 1), (365, 1464, 3, 0, 4), (365, 1464, 5, 1, 2), (365, 1461, 5, 1, 3),
+    (365, 1464, 5, 0, 15), (365, 1464, 5, 0, 16), (365, 1461, 7, 1, 4), (365, 1464, 7, 1, 5),
+    (365, 1464, 7, 0, 1), (365, 1461, 7, 0, 2), (190, 1464, 7, 1, 1), (190, 1461, 3, 0, 2),
+    (9, 33, 5, 1, 1), (9, 33, 7, 0, 1)])
+def test_u8_call_lengths_either_side_of_the_line(H, W, n, median, T):
+    """The frame counts below and from which a frame of 512 tiles and more runs the
+    matrix kernel, and short calls on smaller frames, which always do."""
+    x = _contents("in turn", T, H, W)
+    p = dsgm.dsgm_params_default(255.0)
+    st = _random(H, W, 1, True, 8)[1]
+    _u8_equals_oracle(x, st, p, n, median)
