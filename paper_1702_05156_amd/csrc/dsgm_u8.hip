@@ -1059,18 +1059,21 @@ hipError_t launch_pre_mfma(PreArgs a, const Blur8& f, hipStream_t stream) {
 
 // The call lengths from which large frames (LARGE8 tiles of 16 x 64 and more) run
 // the matrix kernel; smaller ones always do.  Its set-up and its tiles of half the
-// size have to be paid for by the blur, which without the median's halo and with
-// three taps is too little at any length.  pre_u8_kernel / pre_u8_mfma_kernel on
-// T x 1080 x 1920, us: 5 taps and median T = 1 23.4 / 25.2, 2 32.5 / 32.0, 4 50.1 /
-// 44.0; 7 taps 4 66.8 / 63.3, 6 91.7 / 81.8; 3 taps 2 27.3 / 26.3; without the median 5
-// taps 8 58.8 / 60.4, 32 193.7 / 183.7; 7 taps 2 32.7 / 32.1; 3 taps 32 141.9 / 155.4.
-// On frames without noise (all sums in single precision) 5 taps and median 4 49.7 /
-// 50.8, 7 taps 8 117.8 / 120.9.  480 x 640 (300 tiles): 5 taps and median 1 8.5 / 7.7, 3
-// taps without 32 55.0 / 45.6.
+// size have to be paid for by the blur, which without the median's halo is too
+// little for it with three taps, and with five on frames without noise (all sums
+// in single precision).  pre_u8_kernel / pre_u8_mfma_kernel on T x 1080 x 1920, us:
+// 5 taps and median T = 1 23.4 / 25.2, 2 32.5 / 32.0, 4 50.1 / 44.0; 7 taps 4 66.8 /
+// 63.3, 6 91.7 / 81.8; 3 taps 2 27.3 / 26.3; without the median 3 taps 32 141.9 / 155.4,
+// 5 taps 32 193.7 / 183.7, without noise 195.8 / 242.0, 7 taps 2 32.7 / 32.1, 32 310 /
+// 218, without noise 307 / 324.  Without noise 5 taps and median 4 49.7 / 50.8, 7 taps 8
+// 117.8 / 120.9.  480 x 640 (300 tiles): 5 taps and median 1 8.5 / 7.7, 3 taps without
+// 32 55.0 / 45.6.  Weights that don't fit the fixed point are summed in single precision
+// throughout: a Gaussian of 0.3 pixels, 5 taps and median, 6 x 1080 x 1920 67.9 / 68.2, 32
+// 294 / 285 us, 500 x 240 x 320 1,225 / 739 us.
 constexpr int64_t LARGE8 = 512;
-int64_t matrix_from(int rg, bool median) {
-  if (median) return rg == 1 ? 1 : rg == 2 ? 3 : 5;
-  return rg == 1 ? INT64_MAX : rg == 2 ? 16 : 2;
+int64_t matrix_from(int rg, bool median, bool fits) {
+  if (median) return rg == 1 ? 1 : !fits ? 16 : rg == 2 ? 3 : 5;
+  return rg == 3 && fits ? 2 : INT64_MAX;
 }
 
 template <bool MED, bool PRINTED>
@@ -1081,8 +1084,7 @@ hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
   Blur8 f;
   if (matrix) {
     f = blur_weights(a.w, 2 * rg + 1);
-    matrix = f.width != 0 &&
-             (a.tiles_x * a.tiles_y < LARGE8 || a.T >= matrix_from(rg, MED));
+    matrix = a.tiles_x * a.tiles_y < LARGE8 || a.T >= matrix_from(rg, MED, f.width != 0);
   }
   switch (matrix ? rg + 4 : rg) {
     case 0: hipLaunchKernelGGL((pre_u8_kernel<0, MED, PRINTED>), grid, block, 0, stream, a); break;

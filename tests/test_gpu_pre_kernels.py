@@ -106,7 +106,7 @@ def test_u8_undecided_sums(kind, H, W, n, median):
 
 @pytest.mark.parametrize("H,W,n,median,T", [
     (365, 1461, 3, 1, 1), (365, 1464, 3, 0, 4), (365, 1464, 5, 1, 2), (365, 1461, 5, 1, 3),
-    (365, 1464, 5, 0, 15), (365, 1464, 5, 0, 16), (365, 1461, 7, 1, 4), (365, 1464, 7, 1, 5),
+    (365, 1464, 5, 0, 16), (365, 1461, 7, 1, 4), (365, 1464, 7, 1, 5),
     (365, 1464, 7, 0, 1), (365, 1461, 7, 0, 2), (190, 1464, 7, 1, 1), (190, 1461, 3, 0, 2),
     (9, 33, 5, 1, 1), (9, 33, 7, 0, 1)])
 def test_u8_call_lengths_either_side_of_the_line(H, W, n, median, T):
@@ -116,3 +116,24 @@ def test_u8_call_lengths_either_side_of_the_line(H, W, n, median, T):
     p = dsgm.dsgm_params_default(255.0)
     st = _random(H, W, 1, True, 8)[1]
     _u8_equals_oracle(x, st, p, n, median)
+
+
+@pytest.mark.parametrize("weights", [[-0.2, 0.3, 0.9, 0.3, -0.3], [0.0, 0.05, 0.9, 0.05, 0.0],
+                                     [0.5, 0.5, 0.5, 0.5, 0.5], [1e30, 0.0, 1.0, 0.0, -1e30]])
+@pytest.mark.parametrize("T,H,W", [(3, 45, 131), (16, 365, 1464), (15, 365, 1461)])
+def test_u8_weights_outside_the_fixed_point(weights, T, H, W):
+    """Taps that are negative, too large for the fixed point or sum to more than one
+    (their sums all in single precision; products of infinities and NaN among
+    them): as pre_u8_kernel, which the same call with decision codes runs."""
+    x = torch.as_tensor(_contents("half", T, H, W), device="cuda")
+    p = dsgm.dsgm_params_default(255.0)
+    filt = dsgm.gauss_filter(5, 1.0, True)
+    for i, v in enumerate(weights):
+        filt.weights[i] = v
+    st = _random(H, W, 1, True, 9)[1]
+    st2 = st.clone()
+    a = dsgm.forward_filtered(x, st, p, filt, filtered=True)
+    b = dsgm.forward_filtered(x, st2, p, filt, filtered=True, codes=True)
+    assert torch.equal(a["filtered"], b["filtered"]) and torch.equal(a["masks"], b["masks"])
+    for u, v in zip(st.planes(), st2.planes()):
+        assert torch.equal(u, v)
