@@ -403,8 +403,8 @@ __global__ void __launch_bounds__(256) u8_init_kernel(const FwdArgs a) {
 
 // The appendix's preprocessing as it runs on 8-bit frames, fused into the
 // 8-bit update (one pass over the sequence, like pre_kernel): a workgroup owns
-// a 16 x 64 tile for all frames, each lane four adjacent pixels of one row
-// with their models in registers.  Per frame it stages the tile's raw bytes
+// a 16 x 64 tile (8 x 32 on small frames) for all frames, each lane four (one)
+// adjacent pixels of one row with their models in registers.  Per frame it stages the tile's raw bytes
 // plus a halo of RG + 1 rows and columns in LDS (indices clamped to the frame),
 // computes every blurred byte of the tile and of the median's halo with the
 // two-dimensional single-precision sum of the appendix's blur (window rows
@@ -414,12 +414,12 @@ __global__ void __launch_bounds__(256) u8_init_kernel(const FwdArgs a) {
 // update on it.  Two barriers per frame: after the raw bytes are staged and
 // after the blurred bytes are written; the next frame's bytes are loaded into
 // registers while the current one is filtered.  All tile cell indices come
-// from geom::pre::Geo.  Calls with decision codes, without a blur, or with
-// weights that the fixed-point form below cannot hold run this kernel.
-template <int RG, bool MED, bool PRINTED>
+// from geom::pre::Geo.  Calls with decision codes, without a blur, and those on
+// large frames that matrix_from() names run this kernel.
+template <int RG, bool MED, bool PRINTED, typename Tile>
 __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) {
-  using G = geom::pre::Geo<RG, MED>;
-  constexpr int PX = geom::pre::PX, TH = geom::pre::TH, TW = geom::pre::TW;
+  using G = geom::pre::Geo<RG, MED, Tile>;
+  constexpr int PX = G::PX, TH = G::TH, TW = G::TW;
   constexpr int N = 2 * RG + 1;  // taps per window row
   __shared__ float buf_raw[G::RAW_N];
   __shared__ float buf_gb[RG > 0 ? G::GB_N : 1];
@@ -559,8 +559,8 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
     }
 
     Vec<uint8_t, PX> mk, cd, fv;
-    mk = __builtin_bit_cast(decltype(mk),
-                            frame8<PX, true, true, PRINTED>(s, xs, var_init, tbl, cd));
+    mk = __builtin_bit_cast(decltype(mk), typename fwd::Raw<PX>::type(
+                                              frame8<PX, true, true, PRINTED>(s, xs, var_init, tbl, cd)));
 #pragma unroll
     for (int q = 0; q < PX; ++q) fv.v[q] = uint8_t(xs[q]);
     uint8_t* const filt = static_cast<uint8_t*>(a.filtered);
@@ -1076,9 +1076,25 @@ int64_t matrix_from(int rg, bool median, bool fits) {
   return rg == 3 && fits ? 2 : INT64_MAX;
 }
 
+// The single-precision kernel on 16 x 64 tiles, on small frames 8 x 32: there the
+// chain of a tile's frames bounds the call (16 x 64 / 8 x 32, median only 24 x 240 x
+// 320 34.4 / 18.5 us, 5 taps with codes 65.7 / 33.8; 1 x 70 x 99 5.9 / 4.0).
+template <int RG, bool MED, bool PRINTED>
+hipError_t launch_pre_plain(PreArgs a, hipStream_t stream) {
+  auto go = [&](auto tile, auto kernel) {
+    using Tile = decltype(tile);
+    a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
+    a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
+    hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a);
+    return hipGetLastError();
+  };
+  if (a.tiles_x * a.tiles_y < SMALL8_BELOW)
+    return go(geom::pre::Small{}, pre_u8_kernel<RG, MED, PRINTED, geom::pre::Small>);
+  return go(geom::pre::Big{}, pre_u8_kernel<RG, MED, PRINTED, geom::pre::Big>);
+}
+
 template <bool MED, bool PRINTED>
-hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
-  const dim3 grid = tile_grid(a), block{geom::pre::NT, 1, 1};
+hipError_t launch_pre_rg(const PreArgs& a, int rg, hipStream_t stream) {
   // (decision codes, a debug output, exist on pre_u8_kernel only)
   bool matrix = rg > 0 && !a.codes;
   Blur8 f;
@@ -1086,17 +1102,16 @@ hipError_t launch_pre_rg(PreArgs a, int rg, hipStream_t stream) {
     f = blur_weights(a.w, 2 * rg + 1);
     matrix = a.tiles_x * a.tiles_y < LARGE8 || a.T >= matrix_from(rg, MED, f.width != 0);
   }
-  switch (matrix ? rg + 4 : rg) {
-    case 0: hipLaunchKernelGGL((pre_u8_kernel<0, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 1: hipLaunchKernelGGL((pre_u8_kernel<1, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((pre_u8_kernel<2, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 3: hipLaunchKernelGGL((pre_u8_kernel<3, MED, PRINTED>), grid, block, 0, stream, a); break;
-    case 5: return launch_pre_mfma<1, MED, PRINTED>(a, f, stream);
-    case 6: return launch_pre_mfma<2, MED, PRINTED>(a, f, stream);
-    case 7: return launch_pre_mfma<3, MED, PRINTED>(a, f, stream);
+  switch (rg) {
+    case 0: return launch_pre_plain<0, MED, PRINTED>(a, stream);
+    case 1: return matrix ? launch_pre_mfma<1, MED, PRINTED>(a, f, stream)
+                          : launch_pre_plain<1, MED, PRINTED>(a, stream);
+    case 2: return matrix ? launch_pre_mfma<2, MED, PRINTED>(a, f, stream)
+                          : launch_pre_plain<2, MED, PRINTED>(a, stream);
+    case 3: return matrix ? launch_pre_mfma<3, MED, PRINTED>(a, f, stream)
+                          : launch_pre_plain<3, MED, PRINTED>(a, stream);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace u8

@@ -137,3 +137,26 @@ def test_u8_weights_outside_the_fixed_point(weights, T, H, W):
     assert torch.equal(a["filtered"], b["filtered"]) and torch.equal(a["masks"], b["masks"])
     for u, v in zip(st.planes(), st2.planes()):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("H,W", [(190, 1464), (190, 1461), (9, 33)])
+@pytest.mark.parametrize("n,median", [(0, 1), (0, 0), (3, 1), (5, 1), (7, 1), (5, 0)])
+def test_u8_single_precision_kernel_on_both_tiles(H, W, n, median):
+    """Calls with decision codes or without a blur, on 16 x 64 tiles (256 and more)
+    and 8 x 32, ragged and with vector stores."""
+    T = 5
+    x = _contents("in turn", T, H, W)
+    p = dsgm.dsgm_params_default(255.0)
+    st = _random(H, W, 1, True, 10)[1]
+    host = {k: getattr(st, k).cpu().numpy().ravel() for k in PLANES}
+    filt = dsgm.gauss_filter(n, 1.0, median)
+    bare = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), st.clone(), p, filt, filtered=True)
+    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), st, p, filt, filtered=True, codes=True)
+    assert torch.equal(bare["filtered"], out["filtered"]) and torch.equal(bare["masks"], out["masks"])
+    xf = oracle.preprocess_u8(x, oracle.gauss_weights(n, 1.0) if n else None, median=bool(median))
+    G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
+    ref = oracle.forward_u8(xf.reshape(T, -1), host, G.oracle_params(p))
+    G.assert_bit_exact("codes", G.flat(out["codes"]).astype(np.uint8), ref["codes"])
+    G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.uint8), ref["masks"])
+    for k in PLANES:
+        G.assert_bit_exact(k, getattr(st, k).cpu().numpy().ravel(), ref[k].astype(np.uint8))
