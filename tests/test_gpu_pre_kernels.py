@@ -160,3 +160,45 @@ def test_u8_single_precision_kernel_on_both_tiles(H, W, n, median):
     G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.uint8), ref["masks"])
     for k in PLANES:
         G.assert_bit_exact(k, getattr(st, k).cpu().numpy().ravel(), ref[k].astype(np.uint8))
+
+
+@pytest.mark.parametrize("W", [1464, 1461])
+@pytest.mark.parametrize("n,median", [(5, 1), (7, 1), (3, 0), (5, 0), (0, 1)])
+@pytest.mark.parametrize("in_dtype,acc", [(torch.float64, dsgm.ACC_F64), (torch.float32, dsgm.ACC_F64_IO32),
+                                          (torch.float32, dsgm.ACC_F32), (torch.bfloat16, dsgm.ACC_F32)])
+def test_large_tiles_every_precision(in_dtype, acc, n, median, W):
+    """16 x 64 tiles (512 and more) of four pixels per lane, whole and in part:
+    with vector stores (W = 1464) and single ones, all outputs, some and none but the
+    masks.  FP64 state is bit-exact (its FP32 outputs the values rounded once); FP32
+    state's filtered frames agree to 1e-6 and its decisions are the update's on
+    them."""
+    T, H = 3, 365
+    sd = dsgm.STATE_TORCH[acc]
+    p = dsgm.dsgm_params_default(2.0)
+    filt = dsgm.gauss_filter(n, 1.0, median)
+    fr, st = G.device_case(47, T, H, W, in_dtype, sd)
+    st2, st3 = st.clone(), st.clone()
+    out = dsgm.forward_filtered(fr, st, p, filt, bg=True, filtered=True, codes=True, acc=acc)
+    bg = dsgm.forward_filtered(fr, st2, p, filt, bg=True, acc=acc)
+    bare = dsgm.forward_filtered(fr, st3, p, filt, acc=acc)
+    assert torch.equal(bg["bg"], out["bg"])
+    for o, s in ((bg, st2), (bare, st3)):
+        assert torch.equal(o["masks"], out["masks"])
+        for a, b in zip(s.planes(), st.planes()):
+            assert torch.equal(a, b)
+    x, st0 = G.host_case(47, T, H, W, in_dtype, sd)
+    xf = oracle.preprocess(x.reshape(T, H, W), oracle.gauss_weights(n, 1.0) if n else None,
+                           median=bool(median)).reshape(T, H * W)
+    if acc == dsgm.ACC_F32:
+        assert np.max(np.abs(G.flat(out["filtered"]) - xf)) <= 1e-6
+        again = dsgm.forward(out["filtered"], G.device_case(47, T, H, W, in_dtype, sd)[1], p, bg=True,
+                             codes=True)
+        for k in ("codes", "masks", "bg"):
+            assert torch.equal(out[k], again[k]), k
+        return
+    io = np.float64 if acc == dsgm.ACC_F64 else np.float32
+    G.assert_bit_exact("filtered", out["filtered"].cpu().numpy().reshape(T, -1), xf.astype(io))
+    ref = oracle.forward(xf, st0, G.oracle_params(p))
+    G.assert_bit_exact("codes", G.flat(out["codes"]).astype(np.uint8), ref["codes"])
+    G.assert_bit_exact("masks", G.flat(out["masks"]).astype(np.uint8), ref["masks"])
+    G.assert_bit_exact("bg", out["bg"].cpu().numpy().reshape(T, -1), ref["bg"].astype(io))
