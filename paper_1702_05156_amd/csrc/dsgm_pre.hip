@@ -343,11 +343,23 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
     // all of them inside one test for whole vectors (24 x 1080 x 1920, FP32 state,
     // bg and filtered frames: 165 us; with the test in each output's store 202)
     const int64_t o = t * a.frame_stride + foff;
+    // FP64 state on large tiles without the median: the codes are formed in every
+    // call.  The code compiled around them runs faster (5 taps, 24 x 721 x 1279 88
+    // against 97 us, FP32 arrays with bg 92 / 109; its registers or wavefronts are not
+    // why: held to 3 wavefronts a SIMD the other form stays at 96).  With the median
+    // it is slower (116 / 110).
+    constexpr bool CODES_FIRST = sizeof(Acc) == 8 && !MED && PX == 4;
+    Vec<uint8_t, PX> cd;
+    if constexpr (CODES_FIRST) {
+#pragma unroll
+      for (int q = 0; q < PX; ++q) cd.v[q] = uint8_t(code_of<Acc>(rec[q]));
+    }
     auto outputs = [&](auto store) {
       store(a.masks, [&](int q) { return mk.v[q]; });
       if (a.bg) store(static_cast<Io*>(a.bg), [&](int q) { return Io(s[q].mA); });
       if (a.filtered) store(static_cast<Io*>(a.filtered), [&](int q) { return Io(xs[q]); });
-      if (a.codes) store(a.codes, [&](int q) { return uint8_t(code_of<Acc>(rec[q])); });
+      if (a.codes)
+        store(a.codes, [&](int q) { return CODES_FIRST ? cd.v[q] : uint8_t(code_of<Acc>(rec[q])); });
     };
     if (vec_ok) {
       outputs([&](auto* out, auto value) {
