@@ -122,13 +122,15 @@ __global__ void __launch_bounds__(256) warp_kernel(const WarpArgs a) {
     s.vA = g[1];
     s.mC = g[2];
     s.vC = g[3];
-    s.aA = age_in<Acc>(age_a);
-    s.aC = age_in<Acc>(age_c);
+    s.aA = age_a;
+    s.aC = age_c;
   } else {
     s.mA = s.mC = x;
     s.vA = s.vC = k.var_init;
-    s.aA = s.aC = age_in<Acc>(1);
+    s.aA = s.aC = 1;
   }
+  convert_ages(s);  // (behind the table's barrier: converted where they are gathered they
+                    // hold it up, 240 x 320 FP32 3.7 us a frame against 3.4)
 
   StepRecord<Acc> r = step_core<Acc>(s, x, k, tbl);
   if (r.swap_lanes != 0) exchange<Acc>(s, x, k, r);
