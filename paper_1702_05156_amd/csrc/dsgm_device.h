@@ -349,6 +349,35 @@ __device__ __forceinline__ int slot_of(const Model<Acc>& s, const uint64_t hit_a
   return idx;
 }
 
+// The same update by selects: the matched model (or C, to be reset) is selected,
+// updated and selected back.  More instructions than update_in_place, but fewer one
+// after the other: each write of a lane mask waits for the instructions before
+// it.  `idx` is the step's table offset, qa as in update_in_place.
+template <typename Acc>
+__device__ __forceinline__ Acc update_selected(Model<Acc>& s, const Acc x, const bool hit_a,
+                                               const bool hit_c,
+                                               const TableEntry<Acc>* __restrict__ tbl, int& idx,
+                                               Acc& qa) {
+  const bool a = lane_mask(hit_a);
+  const int ic = hit_c ? s.aC : reset_age<Acc>();
+  idx = a ? s.aA : ic;
+  const Acc m = a ? s.mA : s.mC;
+  const Acc v = a ? s.vA : s.vC;
+  const TableEntry<Acc> e = entry_at(tbl, idx);
+  const Acc mn = blend(e.u, m, e.w, x);
+  const Acc d = mn - x;
+  const Acc V = d * d;
+  const Acc vn = blend(e.u, v, e.w, V) + e.r;
+  s.mA = a ? mn : s.mA;
+  s.vA = a ? vn : s.vA;
+  s.aA = a ? e.next : s.aA;
+  s.mC = a ? s.mC : mn;
+  s.vC = a ? s.vC : vn;
+  s.aC = a ? s.aC : e.next;
+  qa = a ? V : qa;
+  return d;
+}
+
 // The mask bytes of P pixels from the lane masks of their background tests:
 // 255 except in byte q of the lanes of bg[q], cleared under the masks.
 template <int P>
@@ -391,7 +420,7 @@ __device__ __forceinline__ uint32_t mask_bytes(const uint64_t (&bg)[P]) {
 // squared distance (mA - x)^2 after the update (QD only): the update's d*d if
 // A matched, else the A test's distance (x - mA is the exact negation of
 // mA - x, so the square is the same number).
-template <typename Acc, bool QD = true>
+template <typename Acc, bool QD = true, bool SELECT = false>
 __device__ __forceinline__ StepRecord<Acc> step_core(Model<Acc>& s, const Acc x,
                                                      const StepConsts<Acc>& k,
                                                      const TableEntry<Acc>* __restrict__ tbl) {
@@ -412,9 +441,13 @@ __device__ __forceinline__ StepRecord<Acc> step_core(Model<Acc>& s, const Acc x,
   StepRecord<Acc> r;
   r.hitA = __builtin_amdgcn_inverse_ballot_w64(hit_a);
   r.hitC = hitC && !r.hitA;
-  r.idx = slot_of<Acc>(s, hit_a, hitC);
-  const TableEntry<Acc> e = entry_at(tbl, r.idx);
-  r.d = update_in_place<QD>(s, x, e, hit_a, qA);
+  if constexpr (SELECT) {
+    r.d = update_selected<Acc>(s, x, r.hitA, hitC, tbl, r.idx, qA);
+  } else {
+    r.idx = slot_of<Acc>(s, hit_a, hitC);
+    const TableEntry<Acc> e = entry_at(tbl, r.idx);
+    r.d = update_in_place<QD>(s, x, e, hit_a, qA);
+  }
   r.qd = qA;
   r.swap_lanes = __builtin_amdgcn_ballot_w64(s.aC > s.aA);
   r.swap = __builtin_amdgcn_inverse_ballot_w64(r.swap_lanes);

@@ -89,8 +89,9 @@ __device__ __forceinline__ void fill_table(TableEntry<Acc>* tbl, int weight_rule
 // only) adds the per-frame foreground counts of instances that have counters.
 // F_STEP (one-frame launches without checkpoints or codes) requests the state
 // and the frame before the workgroup builds its table, and has no frame loop.
+// F_SELECT (one pixel per lane) updates by selects instead of under lane masks.
 enum : int { F_BG = FWD_BG, F_CODES = FWD_CODES, F_CKPT = FWD_CKPT, F_PRINTED = FWD_PRINTED,
-             F_COUNT = 16, F_STEP = 32 };
+             F_COUNT = 16, F_STEP = 32, F_SELECT = 64 };
 
 // Everything one lane needs to run its pixel group through T frames.
 struct GroupJob {
@@ -204,7 +205,7 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
 
   auto do_frame = [&](const Vec<In, P>& xin, int64_t t) {
     if (CKPT) {
-      if (ck_left == 0) {
+      if (__builtin_expect(ck_left == 0, 0)) {
         char* planes[6] = {ck_slot, ck_slot + j.ckpt_fplane, ck_slot + 2 * j.ckpt_fplane,
                            ck_slot + 3 * j.ckpt_fplane, ck_slot + 4 * j.ckpt_fplane,
                            ck_slot + 4 * j.ckpt_fplane + j.ckpt_aplane};
@@ -223,10 +224,10 @@ __device__ __forceinline__ void run_group(const GroupJob& j, const StepConsts<Ac
 #pragma unroll
     for (int q = 0; q < P; ++q) {
       xs[q] = to_acc<In, Acc>(xin.v[q]);
-      r[q] = step_core<Acc>(s[q], xs[q], k, tbl);
+      r[q] = step_core<Acc, true, (FLAGS & F_SELECT) != 0>(s[q], xs[q], k, tbl);
       any |= r[q].swap_lanes;
     }
-    if (any != 0) {
+    if (__builtin_expect(any != 0, 0)) {
 #pragma unroll
       for (int q = 0; q < P; ++q) exchange<Acc>(s[q], xs[q], k, r[q]);
     }
@@ -471,17 +472,17 @@ hipError_t launch_fwd_v(const FwdArgs& a, int block, hipStream_t stream) {
 // runtime flags -> compile-time variant.  Decision codes are a debug output:
 // they only exist as one-pixel-per-lane variants (results do not depend on P),
 // so the caller must size the grid for P = 1 when it asks for codes.
-template <typename In, typename Acc, typename Io, int P>
+template <typename In, typename Acc, typename Io, int P, int MORE = 0>
 hipError_t launch_fwd_p(const FwdArgs& a, int flags, int block, hipStream_t stream) {
   switch (flags & (F_BG | F_CKPT | F_PRINTED)) {
-    case 0: return launch_fwd_v<In, Acc, Io, P, 0>(a, block, stream);
-    case F_BG: return launch_fwd_v<In, Acc, Io, P, F_BG>(a, block, stream);
-    case F_CKPT: return launch_fwd_v<In, Acc, Io, P, F_CKPT>(a, block, stream);
-    case F_BG | F_CKPT: return launch_fwd_v<In, Acc, Io, P, F_BG | F_CKPT>(a, block, stream);
-    case F_PRINTED: return launch_fwd_v<In, Acc, Io, P, F_PRINTED>(a, block, stream);
-    case F_BG | F_PRINTED: return launch_fwd_v<In, Acc, Io, P, F_BG | F_PRINTED>(a, block, stream);
-    case F_CKPT | F_PRINTED: return launch_fwd_v<In, Acc, Io, P, F_CKPT | F_PRINTED>(a, block, stream);
-    default: return launch_fwd_v<In, Acc, Io, P, F_BG | F_CKPT | F_PRINTED>(a, block, stream);
+    case 0: return launch_fwd_v<In, Acc, Io, P, MORE>(a, block, stream);
+    case F_BG: return launch_fwd_v<In, Acc, Io, P, MORE | F_BG>(a, block, stream);
+    case F_CKPT: return launch_fwd_v<In, Acc, Io, P, MORE | F_CKPT>(a, block, stream);
+    case F_BG | F_CKPT: return launch_fwd_v<In, Acc, Io, P, MORE | F_BG | F_CKPT>(a, block, stream);
+    case F_PRINTED: return launch_fwd_v<In, Acc, Io, P, MORE | F_PRINTED>(a, block, stream);
+    case F_BG | F_PRINTED: return launch_fwd_v<In, Acc, Io, P, MORE | F_BG | F_PRINTED>(a, block, stream);
+    case F_CKPT | F_PRINTED: return launch_fwd_v<In, Acc, Io, P, MORE | F_CKPT | F_PRINTED>(a, block, stream);
+    default: return launch_fwd_v<In, Acc, Io, P, MORE | F_BG | F_CKPT | F_PRINTED>(a, block, stream);
   }
 }
 
@@ -496,27 +497,44 @@ hipError_t launch_fwd_step(const FwdArgs& a, int flags, int block, hipStream_t s
   }
 }
 
-template <typename In, typename Acc, typename Io>
+template <typename In, typename Acc, typename Io, int MORE>
 hipError_t launch_fwd_codes(const FwdArgs& a, int flags, int block, hipStream_t stream) {
   switch (flags & (F_BG | F_CKPT | F_PRINTED)) {
-    case 0: return launch_fwd_v<In, Acc, Io, 1, F_CODES>(a, block, stream);
-    case F_BG: return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_BG>(a, block, stream);
-    case F_CKPT: return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_CKPT>(a, block, stream);
-    case F_BG | F_CKPT: return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_BG | F_CKPT>(a, block, stream);
-    case F_PRINTED: return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_PRINTED>(a, block, stream);
+    case 0: return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES>(a, block, stream);
+    case F_BG: return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_BG>(a, block, stream);
+    case F_CKPT: return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_CKPT>(a, block, stream);
+    case F_BG | F_CKPT: return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_BG | F_CKPT>(a, block, stream);
+    case F_PRINTED: return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_PRINTED>(a, block, stream);
     case F_BG | F_PRINTED:
-      return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_BG | F_PRINTED>(a, block, stream);
+      return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_BG | F_PRINTED>(a, block, stream);
     case F_CKPT | F_PRINTED:
-      return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_CKPT | F_PRINTED>(a, block, stream);
-    default: return launch_fwd_v<In, Acc, Io, 1, F_CODES | F_BG | F_CKPT | F_PRINTED>(a, block, stream);
+      return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_CKPT | F_PRINTED>(a, block, stream);
+    default: return launch_fwd_v<In, Acc, Io, 1, MORE | F_CODES | F_BG | F_CKPT | F_PRINTED>(a, block, stream);
   }
+}
+
+// Whether a call of one pixel per lane updates by selects (F_SELECT).  With so few
+// wavefronts the chain of a pixel's frames bounds the call, and the lane masks'
+// writes are the longer chain, the more so with checkpoints; with more of them the
+// selects' instructions are what counts.  Masks / selects, us: FP32 state 200 x 121 x
+// 161 (305 wavefronts) 33.3 / 29.8, with bg and checkpoints 42.3 / 37.7; 100 x 301 x
+// 401 (1,887) 22.6 / 21.9; 100 x 480 x 641 (4,808) 33.3 / 37.1; FP64 200 x 121 x 161
+// 36.7 / 34.5 and 48.8 / 44.2; 200 x 209 x 271 (886) 40.5 / 38.6; 200 x 240 x 321
+// (1,204) 46.7 / 48.6; 100 x 360 x 479 (2,694) 34.8 / 38.5.
+template <typename Acc>
+bool selects(const FwdArgs& a) {
+  constexpr int64_t kSimds = 1024;
+  return a.ngroups < (sizeof(Acc) == 4 ? 2 : 1) * kSimds * 64;
 }
 
 template <typename In, typename Acc, typename Io>
 hipError_t launch_fwd_t(const FwdArgs& a, int P, int flags, int block, hipStream_t stream) {
   if (flags & F_CODES) {
     if (P != 1) return hipErrorInvalidValue;  // the caller sizes the grid for P = 1
-    return launch_fwd_codes<In, Acc, Io>(a, flags, block, stream);
+    if constexpr (!is_f32x2<Acc>::value) {
+      if (selects<Acc>(a)) return launch_fwd_codes<In, Acc, Io, F_SELECT>(a, flags, block, stream);
+    }
+    return launch_fwd_codes<In, Acc, Io, 0>(a, flags, block, stream);
   }
   if (a.T == 1 && (flags & F_CKPT) == 0) {
     if (P == 4) return launch_fwd_step<In, Acc, Io, 4>(a, flags, block, stream);
@@ -525,6 +543,9 @@ hipError_t launch_fwd_t(const FwdArgs& a, int P, int flags, int block, hipStream
   }
   if (P == 4) return launch_fwd_p<In, Acc, Io, 4>(a, flags, block, stream);
   if (P == 2) return launch_fwd_p<In, Acc, Io, 2>(a, flags, block, stream);
+  if constexpr (!is_f32x2<Acc>::value) {  // (its update has no lane masks)
+    if (selects<Acc>(a)) return launch_fwd_p<In, Acc, Io, 1, F_SELECT>(a, flags, block, stream);
+  }
   return launch_fwd_p<In, Acc, Io, 1>(a, flags, block, stream);
 }
 
