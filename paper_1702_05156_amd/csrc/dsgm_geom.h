@@ -210,6 +210,64 @@ struct Geo {
     return int(clamp64(gx + d - 1, W - 1) - (x0 - RM));
   }
 };
+
+// The 8-bit form on the matrix cores (dsgm_u8.hip): raw bytes staged as dwords, RP a
+// row; blurred bytes one to a dword, GBP a row.  A matrix product takes 16 windows
+// of 16 bytes in four rows, and lane m + 16 * rgrp of a wavefront gets cells 4 * rgrp
+// .. + 3 of the OW that window m of the group gives.
+template <int RG, bool MED, typename Tile>
+struct Geo8 {
+  using G = Geo<RG, MED, Tile>;
+  static constexpr int N = 2 * RG + 1;
+  static constexpr int OW = RG < 3 ? 12 : 8;               // outputs of a window: OW + N - 1 <= 16
+  static constexpr int CG = (G::GB_W + OW - 1) / OW;       // windows of a row
+  static constexpr int GBP = CG * OW;                      // pitch of the blurred tile, cells
+  static constexpr int DW = (G::RAW_W + 3) / 4;            // staged dwords of a raw row
+  static constexpr int RP = (OW * (CG - 1) + 16) / 4 > DW ? (OW * (CG - 1) + 16) / 4 : DW;
+  static constexpr int CELLS = G::RAW_H * DW;              // staged dwords of a tile
+  static constexpr int LD = (CELLS + NT - 1) / NT;
+  static constexpr int WIN = G::GB_H * CG;                 // windows of a tile
+  static constexpr int GROUPS = (WIN + 15) / 16;
+  static constexpr int SETS = N > 4 ? 2 : 1;               // products per group and digit
+  static constexpr int QR = (G::GB_W + 3) / 4;             // four-cell groups of a blurred row
+  static constexpr int QUADS = G::GB_H * QR;
+  static_assert(4 * SETS > N, "a row of zeros");
+  static_assert(OW + N - 1 <= 16 && OW % 4 == 0, "a window's outputs read its 16 bytes");
+  static_assert(QUADS <= NT, "one four-cell group a lane");
+
+  // a lane's l-th staged dword: which, its place, and where its b-th byte comes from
+  // (clamped to the frame); `inner`: no column of the tile's dwords leaves the
+  // frame, so that a dword is four adjacent bytes
+  DSGM_HD static int stage_cell(int tid, int l) { return tid + l * NT; }
+  DSGM_HD static bool staged(int tid, int l) { return l + 1 < LD || stage_cell(tid, l) < CELLS; }
+  DSGM_HD static int stage_slot(int i) { return i / DW * RP + i % DW; }
+  DSGM_HD static bool inner(int64_t x0, int64_t W) {
+    return x0 >= G::R && x0 - G::R + 4 * DW <= W;
+  }
+  DSGM_HD static int64_t stage_source(int i, int b, int64_t y0, int64_t x0, int64_t H, int64_t W,
+                                      int64_t row_stride) {
+    return clamp64(y0 - G::R + i / DW, H - 1) * row_stride +
+           clamp64(x0 - G::R + 4 * (i % DW) + b, W - 1);
+  }
+  // window `win` of the tile (those past the last stand for the first): its row and
+  // first column in the blurred tile; the first of the four raw dwords of its row
+  // dy (rows past the window carry zero weights and read its last); whether a lane
+  // has cells of it, and where they go
+  DSGM_HD static int win_row(int win) { return win < WIN ? win / CG : 0; }
+  DSGM_HD static int win_col(int win) { return win < WIN ? win % CG * OW : 0; }
+  DSGM_HD static int win_src(int wr, int wc, int dy) {
+    return (wr + (dy < N ? dy : N - 1)) * RP + wc / 4;
+  }
+  DSGM_HD static bool takes(int win, int rgrp) {
+    return win < WIN && 4 * rgrp < OW && win_col(win) + 4 * rgrp < G::GB_W;
+  }
+  DSGM_HD static int win_dst(int wr, int wc, int rgrp) { return wr * GBP + wc + 4 * rgrp; }
+  // the dword that holds the first column of a cell's own window
+  DSGM_HD static int cell_src(int wr, int col) { return wr * RP + col / 4; }
+  // the c-th four cells summed in single precision: first raw dword and place
+  DSGM_HD static int quad_src(int c) { return c / QR * RP + c % QR; }
+  DSGM_HD static int quad_dst(int c) { return c / QR * GBP + 4 * (c % QR); }
+};
 }  // namespace pre
 
 // ------------------------------------------- motion-compensated source pixel

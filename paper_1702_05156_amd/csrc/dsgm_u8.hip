@@ -642,26 +642,6 @@ constexpr uint32_t DENSE8 = 4;
 
 typedef int32_t V4 __attribute__((ext_vector_type(4)));
 
-template <int RG, bool MED, typename Tile>
-struct Geo8 {
-  using G = geom::pre::Geo<RG, MED, Tile>;
-  static constexpr int N = 2 * RG + 1;
-  static constexpr int OW = RG < 3 ? 12 : 8;               // outputs of a window: OW + N - 1 <= 16
-  static constexpr int CG = (G::GB_W + OW - 1) / OW;       // windows of a row
-  static constexpr int GBP = CG * OW;                      // pitch of the blurred tile, cells
-  static constexpr int DW = (G::RAW_W + 3) / 4;            // staged dwords of a raw row
-  static constexpr int RP = (OW * (CG - 1) + 16) / 4 > DW ? (OW * (CG - 1) + 16) / 4 : DW;
-  static constexpr int CELLS = G::RAW_H * DW;              // staged dwords of a tile
-  static constexpr int LD = (CELLS + geom::pre::NT - 1) / geom::pre::NT;
-  static constexpr int WIN = G::GB_H * CG;                 // windows of a tile
-  static constexpr int GROUPS = (WIN + 15) / 16;
-  static constexpr int SETS = N > 4 ? 2 : 1;               // products per group and digit
-  static constexpr int QR = (G::GB_W + 3) / 4;             // four-cell groups of a blurred row
-  static constexpr int QUADS = G::GB_H * QR;
-  static_assert(4 * SETS > N, "a row of zeros");
-  static_assert(OW + N - 1 <= 16 && OW % 4 == 0, "a window's outputs read its 16 bytes");
-};
-
 __device__ __forceinline__ uint32_t min3u(uint32_t a, uint32_t b, uint32_t c) {
   uint32_t r;
   asm("v_min3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -693,7 +673,7 @@ template <int RG, bool MED, bool PRINTED, typename Tile>
 __global__ void __launch_bounds__(geom::pre::NT)
     __attribute__((amdgpu_waves_per_eu(RG == 1 ? 5 : 4)))  // 3 taps, noise: 291 us at 5, 330 at 4
     pre_u8_mfma_kernel(const PreArgs a, const Blur8 f) {
-  using E = Geo8<RG, MED, Tile>;
+  using E = geom::pre::Geo8<RG, MED, Tile>;
   using G = typename E::G;
   constexpr int N = E::N, PX = G::PX, TH = G::TH, TW = G::TW, NT = geom::pre::NT;
   __shared__ alignas(16) uint32_t raw[G::RAW_H * E::RP];   // bytes with the top bit flipped
@@ -711,17 +691,15 @@ __global__ void __launch_bounds__(geom::pre::NT)
 
   // this lane's staged dwords: frame row offset, first column, LDS index.  Where
   // no column of the tile leaves the frame a dword is one (unaligned) load.
-  const bool inner = x0 >= G::R && x0 - G::R + 4 * E::DW <= a.W;
+  const bool inner = E::inner(x0, a.W);
   uint32_t off[E::LD][4], slot[E::LD];  // the four bytes' frame offsets (< 2^31, host check)
 #pragma unroll
   for (int l = 0; l < E::LD; ++l) {
-    const int i = tid + l * NT < E::CELLS ? tid + l * NT : 0;
-    const int r = i / E::DW, c = i - r * E::DW;
-    const int64_t row = geom::clamp64(y0 - G::R + r, a.H - 1) * a.row_stride;
+    const int i = E::staged(tid, l) ? E::stage_cell(tid, l) : 0;
 #pragma unroll
     for (int b = 0; b < 4; ++b)
-      off[l][b] = uint32_t(row + geom::clamp64(x0 - G::R + 4 * c + b, a.W - 1));
-    slot[l] = uint32_t(r * E::RP + c);
+      off[l][b] = uint32_t(E::stage_source(i, b, y0, x0, a.H, a.W, a.row_stride));
+    slot[l] = uint32_t(E::stage_slot(i));
   }
   // the median's rows and columns in the blurred tile, clamped to the frame
   int gr[3], gc[PX + 2];
@@ -810,7 +788,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
     // 1. stage the raw bytes, then start loading the next frame's
 #pragma unroll
     for (int l = 0; l < E::LD; ++l)
-      if (l + 1 < E::LD || tid + l * NT < E::CELLS) raw[slot[l]] = nxt[l] ^ 0x80808080u;
+      if (E::staged(tid, l)) raw[slot[l]] = nxt[l] ^ 0x80808080u;
     __syncthreads();
     if (t + 1 < a.T) load_frame(t + 1);
 
@@ -821,8 +799,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
       // every sum in the appendix's order, four adjacent cells a lane
 #pragma unroll 1
       for (int c = tid; c < E::QUADS; c += NT) {
-        const int r = c / E::QR, q0 = c - r * E::QR;
-        const uint32_t* src = raw + r * E::RP + q0;
+        const uint32_t* src = raw + E::quad_src(c);
         float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int y = 0; y < N; ++y) {
@@ -846,18 +823,15 @@ __global__ void __launch_bounds__(geom::pre::NT)
           any |= __builtin_fabsf(sum[i] - __builtin_rintf(sum[i])) < near && sum[i] > 0.5f;
         }
         n_undecided += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(any)));
-        *reinterpret_cast<Vec<uint32_t, 4>*>(gb + r * E::GBP + 4 * q0) = out;
+        *reinterpret_cast<Vec<uint32_t, 4>*>(gb + E::quad_dst(c)) = out;
       }
     } else {
       for (int grp = wave; grp < E::GROUPS; grp += NT / 64) {
-        const int win = grp * 16 + m, wr = win < E::WIN ? win / E::CG : 0;
-        const int wc = win < E::WIN ? (win - wr * E::CG) * E::OW : 0;
+        const int win = grp * 16 + m, wr = E::win_row(win), wc = E::win_col(win);
         V4 acc[3] = {V4{centre, centre, centre, centre}, V4{0, 0, 0, 0}, V4{0, 0, 0, 0}};
 #pragma unroll
         for (int st = 0; st < E::SETS; ++st) {
-          // rows past the window carry zero weights; they read its last row
-          const int dy = 4 * st + rgrp < N ? 4 * st + rgrp : N - 1;
-          const uint32_t* src = raw + (wr + dy) * E::RP + wc / 4;
+          const uint32_t* src = raw + E::win_src(wr, wc, 4 * st + rgrp);
           const V4 B = {int32_t(src[0]), int32_t(src[1]), int32_t(src[2]), int32_t(src[3])};
 #pragma unroll
           for (int q = 0; q < 3; ++q)
@@ -872,7 +846,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
           out[i] = sum >> 24;
           frac[i] = sum << 8;
         }
-        const bool mine = win < E::WIN && 4 * rgrp < E::OW && wc + 4 * rgrp < G::GB_W;
+        const bool mine = E::takes(win, rgrp);
         const uint32_t low = frac[0] < frac[1] ? frac[0] : frac[1];
         if (__builtin_amdgcn_ballot_w64(mine && min3u(low, frac[2], frac[3]) < width8) != 0) {
           // an integer (not zero: the sum is not negative) lies too near one of the
@@ -887,7 +861,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
             const int i = todo != 0 ? __builtin_ctz(todo) : 0;
             // (a lane that is done reads its window's first columns)
             const int col = todo != 0 ? wc + 4 * rgrp + i : wc, sh = col & 3;
-            const uint32_t* src = raw + wr * E::RP + col / 4;
+            const uint32_t* src = raw + E::cell_src(wr, col);
             // a window row's N bytes lie in at most three dwords
             uint32_t d[N][3];
 #pragma unroll
@@ -914,7 +888,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
           }
         }
         if (mine) {
-          uint32_t* dst = gb + wr * E::GBP + wc + 4 * rgrp;
+          uint32_t* dst = gb + E::win_dst(wr, wc, rgrp);
           *reinterpret_cast<Vec<uint32_t, 4>*>(dst) = Vec<uint32_t, 4>{{out[0], out[1], out[2], out[3]}};
         }
       }
