@@ -77,10 +77,11 @@ def _contents(kind, T, H, W):
     return frames.astype(np.uint8)
 
 
-def _u8_equals_oracle(x, st, p, n, median, sigma=1.0):
-    """The call without decision codes: filtered bytes, masks and state."""
+def _u8_equals_oracle(x, st, p, n, median, sigma=1.0, view=None):
+    """The call without decision codes: filtered bytes, masks and state (`view`:
+    the frames on the device, where they lie otherwise than densely)."""
     host = {k: getattr(st, k).cpu().numpy().ravel() for k in PLANES}
-    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda"), st, p,
+    out = dsgm.forward_filtered(torch.as_tensor(x, device="cuda") if view is None else view, st, p,
                                 dsgm.gauss_filter(n, sigma, median), filtered=True)
     xf = oracle.preprocess_u8(x, oracle.gauss_weights(n, sigma), median=bool(median))
     G.assert_bit_exact("filtered", out["filtered"].cpu().numpy(), xf)
@@ -137,6 +138,30 @@ def test_u8_weights_outside_the_fixed_point(weights, T, H, W):
     assert torch.equal(a["filtered"], b["filtered"]) and torch.equal(a["masks"], b["masks"])
     for u, v in zip(st.planes(), st2.planes()):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("T,H,W", [(3, 1, 1), (4, 1, 70), (4, 70, 1), (5, 16, 64), (2, 17, 65), (3, 2, 3),
+                                   (9, 31, 5)])
+@pytest.mark.parametrize("n,median", [(3, 1), (5, 1), (7, 1), (3, 0), (5, 0), (7, 0)])
+def test_u8_edge_shapes(T, H, W, n, median):
+    """Frames of less than a tile, a window or a dword, and just more than a tile."""
+    x = _contents("in turn", T, H, W)
+    _u8_equals_oracle(x, _random(H, W, 1, True, 11)[1], dsgm.dsgm_params_default(255.0), n, median)
+
+
+@pytest.mark.parametrize("wr,mr", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("T,H,W,n,median", [(19, 21, 70, 3, 1), (19, 21, 70, 7, 0), (18, 190, 1464, 5, 1),
+                                            (5, 365, 1461, 7, 1), (5, 365, 1464, 7, 0)])
+def test_u8_rules_and_padded_rows(wr, mr, T, H, W, n, median):
+    """Both weight and both mask rules on both of the matrix kernel's tiles, on a
+    view whose rows and frames lie apart, at an odd address."""
+    p = dsgm.dsgm_params_default(255.0, mr)
+    p.weight_rule = wr
+    big = torch.full((T, H + 3, W + 13), 255, dtype=torch.uint8, device="cuda")
+    view = big[:, 2:H + 2, 5:W + 5]
+    x = _contents("half", T, H, W)
+    view.copy_(torch.as_tensor(x))
+    _u8_equals_oracle(x, _random(H, W, 1, True, 12)[1], p, n, median, view=view)
 
 
 @pytest.mark.parametrize("H,W", [(190, 1464), (190, 1461), (9, 33)])
