@@ -161,11 +161,12 @@ constexpr int kTuneCkptEvery = 32;
 // Preferred pixels per lane of frames that fill the chip (filling_vector narrows
 // them for others), measured at 1920x2560x500: FP64 and FP32 state run fastest
 // with 2 (more waves per SIMD), BF16 frames with 4 (wider loads of the narrow
-// frames).
-int preferred_vector(int in_dtype, int acc) {
-  if (in_dtype == DSGM_IN_BF16) return 4;
-  (void)acc;
-  return 2;
+// frames).  One frame with double state reads and writes that state mostly: 2 also
+// for BF16 frames (4 / 2: 1 x 720 x 1280 11.6 / 10.0 us, 1 x 1080 x 1920 28.6 / 26.2,
+// 1 x 2160 x 3840 89.2 / 85.0).
+int preferred_vector(int in_dtype, int acc, bool one_frame = false) {
+  const bool double_state = acc == DSGM_ACC_F64 || acc == DSGM_ACC_F64_IO32;
+  return in_dtype == DSGM_IN_BF16 && !(one_frame && double_state) ? 4 : 2;
 }
 
 // Pixels per lane, at most P, at which a frame of px pixels still gives every
@@ -397,7 +398,7 @@ int forward_impl(const void* frames, dsgm_in_dtype in_dtype, dsgm_shape shape, d
   // pixels per lane the layout allows: sizes, strides and every base pointer,
   // the checkpoint's included
   auto legal = [&](int v) { return widest % v == 0 && (!ckpt || aligned(ckpt, ae * v)); };
-  int P = std::min(widest, preferred_vector(in_dtype, acc));
+  int P = std::min(widest, preferred_vector(in_dtype, acc, shape.T == 1));
   if (!legal(P)) P = 1;
   if (as_run) P = widest;  // four one-byte pixels per lane when the layout allows
   P = filling_vector(px, P, acc);

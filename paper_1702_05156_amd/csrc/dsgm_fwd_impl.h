@@ -89,9 +89,10 @@ __device__ __forceinline__ void fill_table(TableEntry<Acc>* tbl, int weight_rule
 // only) adds the per-frame foreground counts of instances that have counters.
 // F_STEP (one-frame launches without checkpoints or codes) requests the state
 // and the frame before the workgroup builds its table, and has no frame loop.
-// F_SELECT (one pixel per lane) updates by selects instead of under lane masks.
+// F_LATE (F_STEP only) requests the frame after the table instead.
+// F_SELECT updates by selects instead of under lane masks.
 enum : int { F_BG = FWD_BG, F_CODES = FWD_CODES, F_CKPT = FWD_CKPT, F_PRINTED = FWD_PRINTED,
-             F_COUNT = 16, F_STEP = 32, F_SELECT = 64 };
+             F_COUNT = 16, F_STEP = 32, F_SELECT = 64, F_LATE = 128 };
 
 // Everything one lane needs to run its pixel group through T frames.
 struct GroupJob {
@@ -326,6 +327,7 @@ __global__ void __launch_bounds__(256) fwd_kernel(const FwdArgs a) {
   if constexpr ((FLAGS & F_STEP) != 0) {
     // one frame: the state and the frame are requested before the table is
     // built, so that their latency overlaps the table's divisions and barrier
+    // (F_LATE: the state only)
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     const bool active = g < a.ngroups;
     const GroupJob j = step_job(a, geom::group_of(g, a.groups_per_row, P, a.W, a.row_stride));
@@ -333,10 +335,13 @@ __global__ void __launch_bounds__(256) fwd_kernel(const FwdArgs a) {
     Vec<In, P> x0;
     if (active) {
       load_state<Acc, P>(j, s);
-      x0 = ld_stream<In, P>(reinterpret_cast<const In*>(j.frames) + j.foff);
+      if constexpr ((FLAGS & F_LATE) == 0)
+        x0 = ld_stream<In, P>(reinterpret_cast<const In*>(j.frames) + j.foff);
     }
     fill_table<Acc>(tbl, a.weight_rule, a.age_max, a.var_init);
     if (!active) return;  // no barrier follows
+    if constexpr ((FLAGS & F_LATE) != 0)
+      x0 = ld_stream<In, P>(reinterpret_cast<const In*>(j.frames) + j.foff);
     const StepConsts<Acc> k = make_consts<Acc>(a.theta_s, a.theta_d, a.var_init, a.var_floor,
                                                a.mask_floor);
     run_group<In, Acc, Io, P, U, FLAGS>(j, k, tbl, s, &x0);
@@ -486,9 +491,32 @@ hipError_t launch_fwd_p(const FwdArgs& a, int flags, int block, hipStream_t stre
   }
 }
 
-// one-frame launches without checkpoints or codes (F_STEP)
+// One-frame launches without checkpoints or codes.  Large frames request the frame
+// after the table (F_LATE) and, with FP32 state, update by selects: their state no
+// longer stays in the XCDs' 32 MB of L2 from call to call (18 or 34 bytes a pixel),
+// and one burst of all requests then costs more than the latency that it hides.
+// Early / late, us: FP32 900 x 1600 9.15 / 9.23, 1000 x 1800 13.1 / 12.7, 1920 x 2560
+// with bg 38.2 / 35.8; BF16 frames with FP32 state 720 x 1280 5.61 / 6.08, 1080 x 1920
+// 14.2 / 13.3, 1920 x 2560 with bg 37.4 / 35.7; FP64 arithmetic with FP32 bg 1200 x
+// 1920 29.4 / 28.6.  Early for all else: FP64 1400 x 2000 33.2 / 34.9, one pixel per
+// lane 1920 x 2559 FP32 34.9 / 36.8, BF16 with FP32 state at two 1920 x 2562 34.7 /
+// 35.8.
 template <typename In, typename Acc, typename Io, int P>
 hipError_t launch_fwd_step(const FwdArgs& a, int flags, int block, hipStream_t stream) {
+  constexpr int64_t LATE_FROM = int64_t(3) << 19;  // pixels
+  constexpr bool late = P > 1 && !is_f32x2<Acc>::value && sizeof(Io) == 4 &&
+                        !(P == 2 && sizeof(In) == 2 && sizeof(Acc) == 4);
+  if constexpr (late) {
+    constexpr int LATE = F_STEP | F_LATE | (sizeof(Acc) == 4 ? F_SELECT : 0);
+    if (a.ngroups * P >= LATE_FROM) {
+      switch (flags & (F_BG | F_PRINTED)) {
+        case 0: return launch_fwd_v<In, Acc, Io, P, LATE>(a, block, stream);
+        case F_BG: return launch_fwd_v<In, Acc, Io, P, LATE | F_BG>(a, block, stream);
+        case F_PRINTED: return launch_fwd_v<In, Acc, Io, P, LATE | F_PRINTED>(a, block, stream);
+        default: return launch_fwd_v<In, Acc, Io, P, LATE | F_BG | F_PRINTED>(a, block, stream);
+      }
+    }
+  }
   switch (flags & (F_BG | F_PRINTED)) {
     case 0: return launch_fwd_v<In, Acc, Io, P, F_STEP>(a, block, stream);
     case F_BG: return launch_fwd_v<In, Acc, Io, P, F_STEP | F_BG>(a, block, stream);

@@ -116,3 +116,23 @@ def test_either_form_of_the_update(in_dtype, acc, H):
                 pl = lambda c, px: c.view(-1, c.numel() // -(-T // K))[:, :px * size].contiguous().view(sd)
                 assert torch.equal(pl(o["ckpt"], n * W),
                                    pl(out["ckpt"], H * W).reshape(-1, H, W)[:, rows].reshape(-1, n * W))
+
+
+@pytest.mark.parametrize("printed", [False, True])
+@pytest.mark.parametrize("H", [1023, 1024])
+@pytest.mark.parametrize("in_dtype,acc", MODES + [(torch.bfloat16, dsgm.ACC_F64_IO32)])
+def test_one_large_frame_at_every_width(in_dtype, acc, H, printed, width):
+    """One frame just below and at 3 x 2^19 pixels, from which its request follows
+    the table: every width gives what one pixel per lane gives, whose request never
+    does."""
+    W = 1536
+    p = dsgm.dsgm_params_default(2.0, dsgm.MASK_PRINTED if printed else dsgm.MASK_VARIANCE)
+    fr, st0 = G.device_case(64, 1, H, W, in_dtype, dsgm.STATE_TORCH[acc])
+    for bg in (False, True):
+        runs = []
+        for v in (1, 2, 4):
+            width(v)
+            st = st0.clone()
+            runs.append((dsgm.forward(fr, st, p, bg=bg, acc=acc), st))
+        for r in runs[1:]:
+            _same(r, runs[0], 1, H, W)
