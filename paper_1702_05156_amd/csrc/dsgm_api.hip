@@ -179,6 +179,11 @@ int preferred_vector(int in_dtype, int acc, bool one_frame = false) {
 // 100 x 720 x 1280 (3,600 wavefronts at 4): 74 / 73 / 81 us; 8-bit 200 x 240 x
 // 320: 119 / 71 / 50 us; FP64 500 x 240 x 320: 225 / 124 / 108 us, 200 x 480 x
 // 640 (2,400 wavefronts at 2): 154 / 110 / 116 us.
+// One frame has no chain, but the latency of one pass (state, table, step, stores)
+// asks for wavefronts alike and the lines are close: 4 / 2 / 1, FP32 240 x 320 2.64 /
+// 2.56 / 2.30 us, 480 x 640 3.45 / 3.45 / 3.23; BF16 frames 360 x 480 3.12 / 2.91 / 2.89,
+// 540 x 960 4.21 / 4.32 / 4.40; 8-bit 240 x 320 2.95 / 2.63 / 2.55, 540 x 960 3.58 / 3.74 /
+// 4.09; FP64 2 / 1: 240 x 320 2.80 / 2.73, 480 x 640 4.34 / 4.70.
 int filling_vector(int64_t px, int P, int acc) {
   constexpr int64_t kSimds = 1024;
   const int64_t need = (acc == DSGM_ACC_F32 || acc == DSGM_ACC_U8 ? 3 : 2) * kSimds;

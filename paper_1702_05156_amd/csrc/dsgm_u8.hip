@@ -414,8 +414,8 @@ __global__ void __launch_bounds__(256) u8_init_kernel(const FwdArgs a) {
 // update on it.  Two barriers per frame: after the raw bytes are staged and
 // after the blurred bytes are written; the next frame's bytes are loaded into
 // registers while the current one is filtered.  All tile cell indices come
-// from geom::pre::Geo.  Calls with decision codes, without a blur, and those on
-// large frames that matrix_from() names run this kernel.
+// from geom::pre::Geo.  Runs the calls with decision codes, without a blur, and
+// those for which the matrix kernel does not pay (matrix_pays()).
 template <int RG, bool MED, bool PRINTED, typename Tile>
 __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) {
   using G = geom::pre::Geo<RG, MED, Tile>;
@@ -1026,33 +1026,39 @@ hipError_t launch_pre_mfma(PreArgs a, const Blur8& f, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a, f);
     return hipGetLastError();
   };
-  if (a.tiles_x * a.tiles_y < SMALL8_BELOW)  // tiles of 16 x 64 (the caller's count)
-    return go(Small{}, pre_u8_mfma_kernel<RG, MED, PRINTED, Small>);
+  if constexpr (MED) {  // (matrix_pays() sends no small frames without it)
+    if (a.tiles_x * a.tiles_y < SMALL8_BELOW)  // tiles of 16 x 64 (the caller's count)
+      return go(Small{}, pre_u8_mfma_kernel<RG, MED, PRINTED, Small>);
+  }
   return go(Wide{}, pre_u8_mfma_kernel<RG, MED, PRINTED, Wide>);
 }
 
-// The call lengths from which large frames (LARGE8 tiles of 16 x 64 and more) run
-// the matrix kernel; smaller ones always do.  Its set-up and its tiles of half the
-// size have to be paid for by the blur, which without the median's halo is too
-// little for it with three taps, and with five on frames without noise (all sums
-// in single precision).  pre_u8_kernel / pre_u8_mfma_kernel on T x 1080 x 1920, us:
-// 5 taps and median T = 1 23.4 / 25.2, 2 32.5 / 32.0, 4 50.1 / 44.0; 7 taps 4 66.8 /
-// 63.3, 6 91.7 / 81.8; 3 taps 2 27.3 / 26.3; without the median 3 taps 32 141.9 / 155.4,
-// 5 taps 32 193.7 / 183.7, without noise 195.8 / 242.0, 7 taps 2 32.7 / 32.1, 32 310 /
-// 218, without noise 307 / 324.  Without noise 5 taps and median 4 49.7 / 50.8, 7 taps 8
-// 117.8 / 120.9.  480 x 640 (300 tiles): 5 taps and median 1 8.5 / 7.7, 3 taps without
-// 32 55.0 / 45.6.  Weights that don't fit the fixed point are summed in single precision
-// throughout: a Gaussian of 0.3 pixels, 5 taps and median, 6 x 1080 x 1920 67.9 / 68.2, 32
-// 294 / 285 us, 500 x 240 x 320 1,225 / 739 us.
-constexpr int64_t LARGE8 = 512;
-int64_t matrix_from(int rg, bool median, bool fits) {
-  if (median) return rg == 1 ? 1 : !fits ? 16 : rg == 2 ? 3 : 5;
-  return rg == 3 && fits ? 2 : INT64_MAX;
+// Whether a call runs the matrix kernel, by taps, call length and frame size (tiles of
+// 16 x 64).  Its set-up, and on large frames its tiles of half the size, have to be
+// paid for by the blur.  pre_u8_kernel / pre_u8_mfma_kernel, us.  With the median: T x
+// 1080 x 1920, 5 taps T = 1 23.4 / 25.2, 2 32.5 / 32.0, 4 50.1 / 44.0; 7 taps 4 66.8 /
+// 63.3, 6 91.7 / 81.8; 3 taps 2 27.3 / 26.3; without noise 5 taps 4 49.7 / 50.8, 7 taps 8
+// 117.8 / 120.9; 600 x 800 (494 tiles) 7 taps 1 10.0 / 11.0, a smooth pattern 4 21.7 /
+// 27.0; 480 x 640 (300) 5 taps 1 8.5 / 7.7, 7 taps 4 21.3 / 18.5.  Weights that don't
+// fit the fixed point, summed in single precision throughout: 5 taps 6 x 1080 x 1920
+// 67.9 / 68.2, 32 294 / 285, 500 x 240 x 320 1,225 / 739.  Without the median, whose halo
+// makes most of the windows, three and five taps are too little: 50 x 1080 x 1920 194 /
+// 228 and 280 / 276 (without noise 263 / 350), 100 x 480 x 640 84 / 132 and 108 / 142, 100
+// x 70 x 99 67 / 98 and 85 / 125; seven taps 50 x 1080 x 1920 430 / 329 (440 / 503), 4
+// 47 / 45 (47 / 55), 50 x 600 x 800 121 / 101, 100 x 480 x 640 148 / 169.
+bool matrix_pays(int rg, bool median, bool fits, int64_t T, int64_t tiles) {
+  constexpr int64_t LARGE8 = 400;
+  if (!median) return rg == 3 && fits && T >= 8 && tiles >= LARGE8;
+  return tiles < LARGE8 || T >= (rg == 1 ? 1 : !fits ? 16 : rg == 2 ? 3 : 5);
 }
 
 // The single-precision kernel on 16 x 64 tiles, on small frames 8 x 32: there the
 // chain of a tile's frames bounds the call (16 x 64 / 8 x 32, median only 24 x 240 x
-// 320 34.4 / 18.5 us, 5 taps with codes 65.7 / 33.8; 1 x 70 x 99 5.9 / 4.0).
+// 320 34.4 / 18.5 us, 5 taps with codes 65.7 / 33.8; 1 x 70 x 99 5.9 / 4.0).  Without
+// the median a tile's halo is narrow, and calls of four frames and more take 8 x 32 at
+// any size: 3 / 5 taps 50 x 800 x 1300 167 / 112 and 225 / 152 us, 50 x 1080 x 1920 215 /
+// 194 and 297 / 280, 4 x 1080 x 1920 29.7 / 27.9 and 35.9 / 34.6 (one frame 17.8 / 17.7
+// and 17.3 / 20.3; without the blur 50 x 1080 x 1920 179 / 200).
 template <int RG, bool MED, bool PRINTED>
 hipError_t launch_pre_plain(PreArgs a, hipStream_t stream) {
   auto go = [&](auto tile, auto kernel) {
@@ -1062,7 +1068,7 @@ hipError_t launch_pre_plain(PreArgs a, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a);
     return hipGetLastError();
   };
-  if (a.tiles_x * a.tiles_y < SMALL8_BELOW)
+  if (a.tiles_x * a.tiles_y < SMALL8_BELOW || (RG > 0 && !MED && a.T >= 4))
     return go(geom::pre::Small{}, pre_u8_kernel<RG, MED, PRINTED, geom::pre::Small>);
   return go(geom::pre::Big{}, pre_u8_kernel<RG, MED, PRINTED, geom::pre::Big>);
 }
@@ -1074,14 +1080,20 @@ hipError_t launch_pre_rg(const PreArgs& a, int rg, hipStream_t stream) {
   Blur8 f;
   if (matrix) {
     f = blur_weights(a.w, 2 * rg + 1);
-    matrix = a.tiles_x * a.tiles_y < LARGE8 || a.T >= matrix_from(rg, MED, f.width != 0);
+    matrix = matrix_pays(rg, MED, f.width != 0, a.T, a.tiles_x * a.tiles_y);
   }
   switch (rg) {
     case 0: return launch_pre_plain<0, MED, PRINTED>(a, stream);
-    case 1: return matrix ? launch_pre_mfma<1, MED, PRINTED>(a, f, stream)
-                          : launch_pre_plain<1, MED, PRINTED>(a, stream);
-    case 2: return matrix ? launch_pre_mfma<2, MED, PRINTED>(a, f, stream)
-                          : launch_pre_plain<2, MED, PRINTED>(a, stream);
+    case 1:
+      if constexpr (MED) {
+        if (matrix) return launch_pre_mfma<1, MED, PRINTED>(a, f, stream);
+      }
+      return launch_pre_plain<1, MED, PRINTED>(a, stream);
+    case 2:
+      if constexpr (MED) {
+        if (matrix) return launch_pre_mfma<2, MED, PRINTED>(a, f, stream);
+      }
+      return launch_pre_plain<2, MED, PRINTED>(a, stream);
     case 3: return matrix ? launch_pre_mfma<3, MED, PRINTED>(a, f, stream)
                           : launch_pre_plain<3, MED, PRINTED>(a, stream);
     default: return hipErrorInvalidValue;

@@ -92,7 +92,7 @@ def _u8_equals_oracle(x, st, p, n, median, sigma=1.0, view=None):
 
 
 @pytest.mark.parametrize("kind", ["ramp", "slow ramp", "smooth", "in turn", "half"])
-@pytest.mark.parametrize("H,W", [(37, 150), (190, 1461), (190, 1464)])
+@pytest.mark.parametrize("H,W", [(37, 150), (190, 1461), (190, 1464), (365, 1461)])
 @pytest.mark.parametrize("n,median", [(3, 1), (5, 1), (7, 1), (3, 0), (5, 0), (7, 0)])
 def test_u8_undecided_sums(kind, H, W, n, median):
     """Tiles where most sums do not decide their byte in fixed point: the
@@ -108,11 +108,11 @@ def test_u8_undecided_sums(kind, H, W, n, median):
 @pytest.mark.parametrize("H,W,n,median,T", [
     (365, 1461, 3, 1, 1), (365, 1464, 3, 0, 4), (365, 1464, 5, 1, 2), (365, 1461, 5, 1, 3),
     (365, 1464, 5, 0, 16), (365, 1461, 7, 1, 4), (365, 1464, 7, 1, 5),
-    (365, 1464, 7, 0, 1), (365, 1461, 7, 0, 2), (190, 1464, 7, 1, 1), (190, 1461, 3, 0, 2),
+    (365, 1464, 7, 0, 7), (365, 1461, 7, 0, 8), (365, 1464, 3, 0, 3), (190, 1464, 7, 1, 1), (190, 1461, 3, 0, 2),
     (9, 33, 5, 1, 1), (9, 33, 7, 0, 1)])
 def test_u8_call_lengths_either_side_of_the_line(H, W, n, median, T):
-    """The frame counts below and from which a frame of 512 tiles and more runs the
-    matrix kernel, and short calls on smaller frames, which always do."""
+    """The frame counts below and from which a frame of 529 tiles runs the matrix
+    kernel or 8 x 32 tiles, and short calls on smaller frames."""
     x = _contents("in turn", T, H, W)
     p = dsgm.dsgm_params_default(255.0)
     st = _random(H, W, 1, True, 8)[1]
@@ -151,7 +151,7 @@ def test_u8_edge_shapes(T, H, W, n, median):
 
 @pytest.mark.parametrize("wr,mr", [(0, 0), (1, 0), (0, 1), (1, 1)])
 @pytest.mark.parametrize("T,H,W,n,median", [(19, 21, 70, 3, 1), (19, 21, 70, 7, 0), (18, 190, 1464, 5, 1),
-                                            (5, 365, 1461, 7, 1), (5, 365, 1464, 7, 0)])
+                                            (5, 365, 1461, 7, 1), (9, 365, 1464, 7, 0)])
 def test_u8_rules_and_padded_rows(wr, mr, T, H, W, n, median):
     """Both weight and both mask rules on both of the matrix kernel's tiles, on a
     view whose rows and frames lie apart, at an odd address."""
