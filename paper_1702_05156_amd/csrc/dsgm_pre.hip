@@ -25,7 +25,7 @@
 // adjacent (six in one row, two columns of three rows), so that it reads every
 // value of its windows once; the medians are plain min/max instructions.  With
 // these and the update under lane masks 1080 x 1920 frames, 5 taps and median,
-// went from 516 to 447 us (FP64, 50 frames) and 285 to 237 us (BF16/FP32).
+// went from 469 to 416 us (FP64, 50 frames) and 260 to 227 us (BF16/FP32).
 //
 // Median of nine: sort each of the three columns of the neighbourhood; the
 // median is then the median of (largest column minimum, median of the column
@@ -134,10 +134,10 @@ __device__ __forceinline__ float tap<float>(float acc, float w, float x) {
 // Frames of fewer 16 x 64 tiles than this (two per CU) are cut into 8 x 32 tiles
 // of one pixel per lane: with few workgroups the chain of a tile's frames bounds
 // the call, and a quarter of the pixels per lane shortens it.  16 x 64 against
-// 8 x 32 tiles, 5 taps and median: FP64 500 x 240 x 320 (75 tiles) 791 / 527 us,
-// 100 x 480 x 640 (300) 226 / 176 us, 50 x 720 x 1280 (900) 228 / 233 us,
-// 50 x 1080 x 1920 (2,040) 450 / 525 us; BF16/FP32 601 / 379, 151 / 113,
-// 124 / 142 and 238 / 297 us.
+// 8 x 32 tiles, 5 taps and median: FP64 500 x 240 x 320 (75 tiles) 796 / 518 us,
+// 100 x 480 x 640 (300) 217 / 171 us, 50 x 720 x 1280 (900) 220 / 230 us,
+// 50 x 1080 x 1920 (2,040) 419 / 478 us; BF16/FP32 632 / 365, 150 / 104,
+// 116 / 132 and 230 / 285 us.
 constexpr int64_t SMALL_BELOW = 512;
 
 template <typename In, typename Acc, typename Io, int RG, bool MED, bool PRINTED, typename Tile>

@@ -610,16 +610,18 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 // Without noise many sums are integers (a ramp of one level a pixel: 99 % of the
 // cells are undecided; a flat area: all).  A workgroup that finds DENSE8 lanes or
 // more with undecided cells therefore forms all its sums in single precision, four
-// adjacent cells a lane, until a later look (every eighth frame) finds fewer; its
+// adjacent cells a lane, until a later look (every 16th frame) finds fewer; its
 // first frame it forms so too.  The way does not change a byte.  50 x 1080 x 1920
-// on MI355X, 3 / 5 / 7 taps: ramp 577 / 768 / 1,784 us with every undecided cell
-// by itself, 317 / 440 / 622 us so; pre_u8_kernel below 401 / 477 / 689 us; flat
-// frames 439 and 620 us (5, 7 taps); noise 309 / 333 / 491 and 291 / 337 / 468 us.
-// Limits of 2, 4, 12 and 32 lanes: noise with flat squares on 5 % of the frame
-// 422 / 419 / 419 / 412 us, on 30 % 479 / 484 / 499 / 534 us, a smooth pattern
-// (4 % undecided) 441 / 441 / 491 / 606 us.  Slowest against
+// on MI355X, 3 / 5 / 7 taps: ramp 552 / 769 / 1,790 us with every undecided cell
+// by itself, 319 / 436 / 635 us so; pre_u8_kernel below 330 / 452 / 665 us; flat
+// frames 312 / 435 / 634 us; noise 308 / 333 / 491 and 293 / 333 / 484 us.
+// Limits of 2, 4, 12 and 32 lanes (a look every 8th frame): noise with flat squares
+// on 5 % of the frame 422 / 419 / 419 / 412 us, on 30 % 479 / 484 / 499 / 534 us, a
+// smooth pattern (4 % undecided) 441 / 441 / 491 / 606 us.  A look every 8th and
+// every 16th frame, with the compiler told that both are rare: noise, 100 x 1920 x
+// 2560, 5 taps 1,515 and 1,494 us, 7 taps 2,174 and 2,138 us.  Slowest against
 // pre_u8_kernel is what a look can't foretell: flat squares on 30 % of the frame, at
-// other places in every frame (486 / 478 us; 7 taps 806 / 688 us).
+// other places in every frame (483 / 452 us; 7 taps 822 / 665 us).
 //
 // One matrix product covers 16 windows of 16 bytes in four rows: column n of B
 // is a window (lane n % 16 holds 16 bytes of row lane / 16), row m of A the
@@ -632,11 +634,11 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 // CU; 16 x 64 tiles, four pixels per lane, needed 192 registers (1,047 against
 // 908 us for 50 frames of 1920 x 2560).  Frames of fewer 16 x 64 tiles than
 // SMALL8_BELOW take 8 x 32 tiles, one pixel per lane (8 x 64 / 8 x 32 tiles):
-// 500 x 240 x 320 (75) 699 / 563 us, 100 x 360 x 480 (184) 160 / 129 us,
-// 100 x 480 x 640 (300) 175 / 210 us, 50 x 1080 x 1920 (2,040) 365 / 465 us.
+// 500 x 240 x 320 (75) 722 / 571 us, 100 x 360 x 480 (184) 160 / 125 us,
+// 100 x 480 x 640 (300) 166 / 205 us, 50 x 1080 x 1920 (2,040) 337 / 450 us.
 // Bound by vector issue (about 90 instructions a pixel, half of them the 8-bit
-// update).  pre_u8_kernel, which sums the windows in single precision, took
-// 1,182, 253, 300 and 507 us.
+// update).  pre_u8_kernel, which sums the windows in single precision, takes
+// 600, 140, 278 and 460 us.
 constexpr int64_t SMALL8_BELOW = 256;
 constexpr uint32_t DENSE8 = 4;
 
@@ -793,9 +795,9 @@ __global__ void __launch_bounds__(geom::pre::NT)
     if (t + 1 < a.T) load_frame(t + 1);
 
     // 2. the blurred bytes of the tile and the median's halo
-    const bool look = fixed && (t == 0 || (t & 7) == 7);  // this frame decides the next ones' way
+    const bool look = fixed && (t == 0 || (t & 15) == 15);  // this frame decides the next ones' way
     uint32_t n_undecided = 0;
-    if (plain) {
+    if (__builtin_expect(plain, RG == 1)) {
       // every sum in the appendix's order, four adjacent cells a lane
 #pragma unroll 1
       for (int c = tid; c < E::QUADS; c += NT) {
@@ -855,7 +857,7 @@ __global__ void __launch_bounds__(geom::pre::NT)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             todo |= mine && frac[i] < width8 && out[i] != 0 ? 1u << i : 0u;
-          if (look)
+          if (__builtin_expect(look, 0))
             n_undecided += uint32_t(__builtin_popcountll(__builtin_amdgcn_ballot_w64(todo != 0)));
           while (__builtin_amdgcn_ballot_w64(todo != 0) != 0) {
             const int i = todo != 0 ? __builtin_ctz(todo) : 0;
@@ -893,11 +895,11 @@ __global__ void __launch_bounds__(geom::pre::NT)
         }
       }
     }
-    if (look) {  // (uniform, as the test of the lane is not)
+    if (__builtin_expect(look, 0)) {  // (uniform, as the test of the lane is not)
       if (lane == 0) undecided[wave] = n_undecided;
     }
     __syncthreads();
-    if (look) {
+    if (__builtin_expect(look, 0)) {
       const uint32_t n = undecided[0] + undecided[1] + undecided[2] + undecided[3];
       plain = __builtin_amdgcn_readfirstlane(n) >= DENSE8;
     }

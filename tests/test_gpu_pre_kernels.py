@@ -72,7 +72,7 @@ def _contents(kind, T, H, W):
     ramp = (x + t + 0 * y) % 256
     frames = {"ramp": ramp, "slow ramp": (x + y + t) // 8 % 256,
               "smooth": np.rint(127 + 100 * np.sin((x + t) / 37) * np.cos(y / 29)),
-              "in turn": np.where((t // 5) % 2 == 0, ramp, noise),
+              "in turn": np.where((t // 5) % 2 == 1, ramp, noise),
               "half": np.where(x < W // 2, ramp, noise)}[kind]
     return frames.astype(np.uint8)
 
@@ -98,7 +98,7 @@ def test_u8_undecided_sums(kind, H, W, n, median):
     """Tiles where most sums do not decide their byte in fixed point: the
     appendix's bytes, whichever way they are summed (8 x 32 tiles and, from 256
     tiles of 16 x 64 on, 8 x 64 tiles)."""
-    T = 18
+    T = 36 if H < 200 else 18
     x = _contents(kind, T, H, W)
     p = dsgm.dsgm_params_default(255.0, 1)
     st = _random(H, W, 1, True, 7)[1]
