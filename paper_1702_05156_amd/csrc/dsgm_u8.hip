@@ -636,8 +636,8 @@ __global__ void __launch_bounds__(geom::pre::NT) pre_u8_kernel(const PreArgs a) 
 // SMALL8_BELOW take 8 x 32 tiles, one pixel per lane (8 x 64 / 8 x 32 tiles):
 // 500 x 240 x 320 (75) 722 / 571 us, 100 x 360 x 480 (184) 160 / 125 us,
 // 100 x 480 x 640 (300) 166 / 205 us, 50 x 1080 x 1920 (2,040) 337 / 450 us.
-// Bound by vector issue (about 90 instructions a pixel, half of them the 8-bit
-// update).  pre_u8_kernel, which sums the windows in single precision, takes
+// Bound by vector issue (83 instructions a pixel on noisy frames, half of them the
+// 8-bit update).  pre_u8_kernel, which sums the windows in single precision, takes
 // 600, 140, 278 and 460 us.
 constexpr int64_t SMALL8_BELOW = 256;
 constexpr uint32_t DENSE8 = 4;
