@@ -140,8 +140,17 @@ __device__ __forceinline__ float tap<float>(float acc, float w, float x) {
 // 116 / 132 and 230 / 285 us.
 constexpr int64_t SMALL_BELOW = 512;
 
+// Waves per SIMD the kernel is compiled for: 3 with FP64 state and four pixels per
+// lane (7 taps and median took 169 VGPRs by themselves and ran at 2: one frame of 1920 x
+// 2560 95.0 us, 78.9 at 3), else the compiler's choice.
+template <typename Acc, typename Tile>
+constexpr int pre_waves() {
+  return sizeof(Acc) == 8 && Tile::px == 4 ? 3 : 1;
+}
+
 template <typename In, typename Acc, typename Io, int RG, bool MED, bool PRINTED, typename Tile>
-__global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(pre_waves<Acc, Tile>())))
+pre_kernel(const PreArgs a) {
   using G = Geo<RG, MED, Tile>;
   constexpr int TH = G::TH, TW = G::TW, PX = G::PX;
   // raw, row-blurred and blurred tiles each have their own storage, so a frame
@@ -152,8 +161,15 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
   __shared__ alignas(16) Acc buf_hb[RG > 0 ? G::HB_N : 1];
   __shared__ alignas(16) Acc buf_gb[RG > 0 ? G::GB_N : 1];
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
-  const int64_t tile = tile_here(a);
-  if (tile < 0) return;
+  // FP32 state maps its tile before the table is built, FP64 after it (one frame of
+  // 1920 x 2560, 7 taps and median, before / after: FP32 50.0 / 54.7 us, FP32 arrays
+  // with FP64 state 85.6 / 77.6)
+  constexpr bool MAP_FIRST = sizeof(Acc) == 4;
+  int64_t tile = 0;
+  if constexpr (MAP_FIRST) {
+    tile = tile_here(a);
+    if (tile < 0) return;
+  }
   fill_table<Acc>(tbl, a.weight_rule, a.age_max, a.var_init);  // ends with a barrier
   const StepConsts<Acc> k =
       make_consts<Acc>(a.theta_s, a.theta_d, a.var_init, a.var_floor, a.mask_floor);
@@ -162,6 +178,10 @@ __global__ void __launch_bounds__(NT) pre_kernel(const PreArgs a) {
 #pragma unroll
   for (int i = 0; i < 2 * RG + 1; ++i) wt[i] = Acc(a.w[i]);
 
+  if constexpr (!MAP_FIRST) {
+    tile = tile_here(a);
+    if (tile < 0) return;
+  }
   const int64_t y0 = (tile / a.tiles_x) * TH, x0 = (tile % a.tiles_x) * TW;
   const int tid = threadIdx.x;
   const int ty = G::lane_row(tid), tx = G::lane_col(tid);  // this lane's row and first column
@@ -396,11 +416,16 @@ hipError_t launch_tile(PreArgs a, int rg, hipStream_t stream) {
   a.tiles_x = (a.W + Tile::tw - 1) / Tile::tw;
   a.tiles_y = (a.H + Tile::th - 1) / Tile::th;
   const dim3 grid = tile_grid(a), block{NT, 1, 1};
+  // One frame with FP64 state and no median fits 4 wavefronts a SIMD, whose requests
+  // then come in one burst: LDS that nothing uses holds it to 3 workgroups a CU (5 taps,
+  // 1920 x 2560, 4 / 3: FP64 85.9 / 77.9 us, FP32 arrays 86.6 / 76.7; four frames are
+  // faster at 4, 4 x 721 x 1279 29.3 / 33.7)
+  const uint32_t lds = sizeof(Acc) == 8 && !MED && Tile::px == 4 && a.T == 1 ? 12 * 1024 : 0;
   switch (rg) {
-    case 0: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 0, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
-    case 1: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 1, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
-    case 2: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 2, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
-    case 3: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 3, MED, PRINTED, Tile>), grid, block, 0, stream, a); break;
+    case 0: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 0, MED, PRINTED, Tile>), grid, block, lds, stream, a); break;
+    case 1: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 1, MED, PRINTED, Tile>), grid, block, lds, stream, a); break;
+    case 2: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 2, MED, PRINTED, Tile>), grid, block, lds, stream, a); break;
+    case 3: hipLaunchKernelGGL((pre_kernel<In, Acc, Io, 3, MED, PRINTED, Tile>), grid, block, lds, stream, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
