@@ -1057,8 +1057,9 @@ bool matrix_pays(int rg, bool median, bool fits, int64_t T, int64_t tiles) {
 // The single-precision kernel on 16 x 64 tiles, on small frames 8 x 32: there the
 // chain of a tile's frames bounds the call (16 x 64 / 8 x 32, median only 24 x 240 x
 // 320 34.4 / 18.5 us, 5 taps with codes 65.7 / 33.8; 1 x 70 x 99 5.9 / 4.0).  Without
-// the median a tile's halo is narrow, and calls of four frames and more take 8 x 32 at
-// any size: 3 / 5 taps 50 x 800 x 1300 167 / 112 and 225 / 152 us, 50 x 1080 x 1920 215 /
+// the median a tile's halo is narrow, and frames below MIDDLE8 tiles, and calls of four
+// frames and more at any size, take 8 x 32: 3 / 5 taps 1 x 480 x 640 7.1 / 5.3 and 7.7 /
+// 5.6 us, 50 x 800 x 1300 167 / 112 and 225 / 152 us, 50 x 1080 x 1920 215 /
 // 194 and 297 / 280, 4 x 1080 x 1920 29.7 / 27.9 and 35.9 / 34.6 (one frame 17.8 / 17.7
 // and 17.3 / 20.3; without the blur 50 x 1080 x 1920 179 / 200).
 template <int RG, bool MED, bool PRINTED>
@@ -1070,7 +1071,9 @@ hipError_t launch_pre_plain(PreArgs a, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, tile_grid(a), dim3(geom::pre::NT), 0, stream, a);
     return hipGetLastError();
   };
-  if (a.tiles_x * a.tiles_y < SMALL8_BELOW || (RG > 0 && !MED && a.T >= 4))
+  constexpr int64_t MIDDLE8 = 512;
+  const int64_t tiles = a.tiles_x * a.tiles_y;
+  if (tiles < SMALL8_BELOW || (RG > 0 && !MED && (a.T >= 4 || tiles < MIDDLE8)))
     return go(geom::pre::Small{}, pre_u8_kernel<RG, MED, PRINTED, geom::pre::Small>);
   return go(geom::pre::Big{}, pre_u8_kernel<RG, MED, PRINTED, geom::pre::Big>);
 }
