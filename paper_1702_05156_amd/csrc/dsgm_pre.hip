@@ -161,10 +161,11 @@ pre_kernel(const PreArgs a) {
   __shared__ alignas(16) Acc buf_hb[RG > 0 ? G::HB_N : 1];
   __shared__ alignas(16) Acc buf_gb[RG > 0 ? G::GB_N : 1];
   __shared__ TableEntry<Acc> tbl[TABLE_SIZE];
-  // FP32 state maps its tile before the table is built, FP64 after it (one frame of
-  // 1920 x 2560, 7 taps and median, before / after: FP32 50.0 / 54.7 us, FP32 arrays
-  // with FP64 state 85.6 / 77.6)
-  constexpr bool MAP_FIRST = sizeof(Acc) == 4;
+  // FP32 state and small tiles map their tile before the table is built, FP64 state on
+  // large tiles after it (before / after: 1 x 1920 x 2560, 7 taps and median, FP32 50.0 /
+  // 54.7 us, FP32 arrays with FP64 state 85.6 / 77.6; FP64 500 x 240 x 320, 5 taps and
+  // median 522 / 532)
+  constexpr bool MAP_FIRST = sizeof(Acc) == 4 || PX == 1;
   int64_t tile = 0;
   if constexpr (MAP_FIRST) {
     tile = tile_here(a);
